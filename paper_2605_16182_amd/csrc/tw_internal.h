@@ -74,7 +74,7 @@ constexpr int FENCE_MAX_LEVELS = (32 + FENCE_LOG - 1) / FENCE_LOG + 1;
 static_assert((1 << FENCE_LOG) == FENCE_FAN, "FENCE_FAN must be 2^FENCE_LOG");
 
 // levels above level 0 needed for n groups: 0 when n <= FENCE_FAN
-__host__ __device__ inline int fence_levels(uint64_t n) {
+__host__ __device__ constexpr int fence_levels(uint64_t n) {
     int k = 0;
     while (n > (uint64_t)FENCE_FAN) {
         n = (n + FENCE_FAN - 1) >> FENCE_LOG;
@@ -84,7 +84,7 @@ __host__ __device__ inline int fence_levels(uint64_t n) {
 }
 
 // words stored for level k (k >= 0) of a segment of cap groups
-__host__ __device__ inline uint32_t fence_level_len(uint64_t cap, int k) {
+__host__ __device__ constexpr uint32_t fence_level_len(uint64_t cap, int k) {
     const uint64_t n = (cap + (1ull << (FENCE_LOG * k)) - 1) >> (FENCE_LOG * k);
     return (uint32_t)((n + FENCE_FAN - 1) / FENCE_FAN * FENCE_FAN);
 }
@@ -98,12 +98,28 @@ __host__ __device__ inline uint32_t fence_cap(uint64_t cap) {
     return s;
 }
 
-// word offset of level k inside a segment's fence
-__host__ __device__ inline uint32_t fence_level_off(uint64_t cap, int k) {
-    uint32_t off = 0;
-    for (int j = 0; j < k; ++j) off += fence_level_len(cap, j);
-    return off;
+// word offset of level k <= fence_levels(cap) inside the fence of a segment
+// of cap = 2^lg groups: every level below such a k holds cap >> (FENCE_LOG j)
+// > FENCE_FAN words, so the offset is cap (1 + 1/8 + ... ) with k terms, whose
+// binary digits are k ones three places apart
+__host__ __device__ constexpr uint32_t fence_level_off(uint32_t lg, int k) {
+    static_assert(FENCE_LOG == 3, "0x49249249 has its ones three places apart");
+    return (0x49249249u & ((1u << (FENCE_LOG * k)) - 1u))
+           << ((lg + FENCE_LOG - FENCE_LOG * k) & 31u);
 }
+
+// the closed form against the sum of the levels, for every capacity and level
+constexpr bool fence_level_off_ok() {
+    for (uint32_t lg = FENCE_LOG + 1; lg < 32; ++lg) {
+        uint64_t sum = 0;
+        for (int k = 0; k <= fence_levels(1ull << lg); ++k) {
+            if (fence_level_off(lg, k) != sum) return false;
+            sum += fence_level_len(1ull << lg, k);
+        }
+    }
+    return true;
+}
+static_assert(fence_level_off_ok(), "fence level offsets");
 
 // key shift for a segment whose keys must reach span (keep a 4x margin for
 // later appends before a rewrite)
@@ -128,6 +144,8 @@ __device__ __forceinline__ uint32_t xcd_tile(uint32_t bid, uint32_t nb) {
 __host__ __device__ inline uint64_t seg_groups(uint32_t code) {
     return (uint64_t)FENCE_FAN << code;
 }
+// log2 of the capacity
+__host__ __device__ inline uint32_t seg_lg(uint32_t code) { return FENCE_LOG + code; }
 
 // node2vec adjacency: an open-addressing table (linear probing) of the
 // window's (source, destination) pairs, each with its record count; a pair

@@ -990,7 +990,8 @@ k_hop_coop(const WalkArgs a, Live cur, Live nxt, int32_t* __restrict__ prev_of,
         const int K = (int)rec_levels(r.lv);
         if (K > 0) {
             const uint64_t cap = seg_groups(rec_code(r.lv));
-            const uint64_t top = (uint64_t)r.fence_off + fence_level_off(cap, K) +
+            const uint64_t top = (uint64_t)r.fence_off +
+                                 fence_level_off(seg_lg(rec_code(r.lv)), K) +
                                  fence_level_len(cap, K);  // end of level K
             uint64_t from = top;
             for (int k = K; k >= 0; --k) {

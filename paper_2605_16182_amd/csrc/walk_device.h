@@ -107,23 +107,29 @@ __device__ __forceinline__ uint32_t count_le(const GroupRec* __restrict__ ng, ui
     return a - lo;
 }
 
-// Entries of one 8-word key window <= the query, exactly: keys below q
-// count, keys equal to q are decided by their group's timestamp (group
-// index g0 + (lo + i) * step for entry i).
+// Entries of one 8-word key window <= the query, exactly: with unshifted keys
+// a key orders as its timestamp does; with shifted ones keys below q count and
+// keys equal to q are decided by their group's timestamp (group index g0 +
+// (lo + i) * step for entry i). (On an undirected graph a walk that arrives by
+// an edge always finds its mirror image's key equal to the query: the group
+// read was one more dependent random load in every hop.)
 __device__ __forceinline__ uint32_t window_count(const uint32_t* win, uint32_t q, int64_t t,
-                                                 const GroupRec* __restrict__ ng, uint64_t gbase,
-                                                 uint64_t step) {
+                                                 uint32_t shift, const GroupRec* __restrict__ ng,
+                                                 uint64_t gbase, uint64_t step) {
     const uint4 a = reinterpret_cast<const uint4*>(win)[0];
     const uint4 b = reinterpret_cast<const uint4*>(win)[1];
     const uint32_t k[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-    uint32_t lt = 0, le = 0;
+    uint32_t le = 0;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        lt += k[j] < q;
-        le += k[j] <= q;
+    for (int j = 0; j < 8; ++j) le += k[j] <= q;
+    if (shift != 0) {
+        uint32_t lt = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) lt += k[j] < q;
+        for (uint32_t j = lt; j < le; ++j) lt += ng[gbase + j * step].ts <= t;
+        le = lt;
     }
-    for (uint32_t j = lt; j < le; ++j) lt += ng[gbase + j * step].ts <= t;
-    return lt;
+    return le;
 }
 
 // Gamma lookup (Sec. "Dual-Index Organization": the node's first timestamp
@@ -132,7 +138,12 @@ __device__ __forceinline__ uint32_t window_count(const uint32_t* win, uint32_t q
 // level in use down to level 0. Requires t < r.t_last, so the result is below r.ge.
 // Returns the absolute group index. panel (nullable) holds fence words
 // [panel_base, panel_base + panel_len) in LDS; windows inside it are read
-// from there.
+// from there. The search is a chain of dependent window reads with integer
+// work between them, so both are kept short: level offsets in closed form, the
+// prediction from the 32-bit keys. Against offsets summed over the levels, a
+// prediction by an FP64 division and a group read at equal unshifted keys: 4M
+// exponential walks on 100M edges 3.94 -> 3.75 ms, 1M uniform walks on an
+// undirected 6.7M-edge graph 930 -> 817 us, 1,000 linear walks 97 -> 85 us.
 __device__ __forceinline__ uint32_t fence_search(const GroupRec* __restrict__ ng,
                                                  const uint32_t* __restrict__ fence,
                                                  const NodeRec& r, int64_t t,
@@ -142,55 +153,62 @@ __device__ __forceinline__ uint32_t fence_search(const GroupRec* __restrict__ ng
     if (K == 0) return r.gb + count_le(ng, r.gb, r.ge, t);
     const int64_t base = r.kbase;
     if (t < base) return r.gb;  // every group of the segment is later
-    const uint32_t q = (uint32_t)((uint64_t)(t - base) >> rec_shift(r.lv));
-    const uint64_t cap = seg_groups(rec_code(r.lv));
+    const uint32_t shift = rec_shift(r.lv);
+    const uint32_t q = (uint32_t)((uint64_t)(t - base) >> shift);
+    const uint32_t lg = seg_lg(rec_code(r.lv));
     int k = K;
-    uint64_t lo = 0;
+    uint32_t lo = 0;
     // A deep fence starts lower: at level k0, whose entries are 8^k0 groups
     // apart with 8^k0 about sqrt(n) / 4, the window around the entry that
-    // t's place between the segment's first and last timestamps predicts.
-    // When that window brackets t (a key <= t, and one > t or the level's
-    // end), the descent goes on from there; otherwise from the top.
+    // the query key's place below the last key predicts (in single precision:
+    // the entries are at most about 2^18). When that window brackets t (a key
+    // <= t, and one > t or the level's end), the descent goes on from there;
+    // otherwise from the top, so the prediction never changes the result.
     const uint32_t n = r.ge - r.g0;
     const int k0 = (31 - __clz(n) + 2) / 6;
     if (k0 + 1 < K) {
-        const uint64_t cnt = (n + (1ull << (FENCE_LOG * k0)) - 1) >> (FENCE_LOG * k0);
-        const double fr = (double)(t - base) / (double)(r.t_last - base);
-        const uint64_t e = (uint64_t)(fr * (double)cnt);
-        uint64_t lo0 = e >= 4 ? (e - 4) & ~3ull : 0;  // 16-byte aligned
-        const uint64_t top = ((cnt + FENCE_FAN - 1) & ~(uint64_t)(FENCE_FAN - 1)) - FENCE_FAN;
+        const uint32_t cnt = (uint32_t)(((uint64_t)n + (1u << (FENCE_LOG * k0)) - 1) >>
+                                        (FENCE_LOG * k0));
+        const uint32_t kl = (uint32_t)((uint64_t)(r.t_last - base) >> shift);
+        const uint32_t e =
+            (uint32_t)((float)q * __builtin_amdgcn_rcpf((float)kl) * (float)cnt);
+        uint32_t lo0 = e >= 4 ? (e - 4) & ~3u : 0;  // 16-byte aligned
+        const uint32_t top = ((cnt + FENCE_FAN - 1) & ~(uint32_t)(FENCE_FAN - 1)) - FENCE_FAN;
         if (lo0 > top) lo0 = top;
-        const uint64_t at = r.fence_off + fence_level_off(cap, k0) + lo0;
+        const uint64_t at = (uint64_t)r.fence_off + fence_level_off(lg, k0) + lo0;
         const uint32_t* win = at >= panel_base && at + FENCE_FAN <= panel_base + panel_len
                                   ? panel + (at - panel_base)
                                   : fence + at;
-        const uint32_t c = window_count(win, q, t, ng, r.g0 + (lo0 << (FENCE_LOG * k0)),
+        const uint32_t c = window_count(win, q, t, shift, ng,
+                                        r.g0 + ((uint64_t)lo0 << (FENCE_LOG * k0)),
                                         1ull << (FENCE_LOG * k0));
         if (c >= 1 && (c < FENCE_FAN || lo0 + FENCE_FAN >= cnt)) {
             if (k0 == 0) {
-                const uint32_t res = r.g0 + (uint32_t)lo0 + c;
+                const uint32_t res = r.g0 + lo0 + c;
                 return res < r.gb ? r.gb : res;
             }
             k = k0 - 1;
             lo = (lo0 + c - 1) * FENCE_FAN;
         }
     }
-    uint64_t off = fence_level_off(cap, k);
+    uint32_t off = fence_level_off(lg, k);
     for (; k >= 0; --k) {
-        const uint64_t at = r.fence_off + off + lo;
+        const uint64_t at = (uint64_t)r.fence_off + off + lo;
         const uint32_t* win = at >= panel_base && at + FENCE_FAN <= panel_base + panel_len
                                   ? panel + (at - panel_base)
                                   : fence + at;
-        const uint32_t c =
-            window_count(win, q, t, ng, r.g0 + (lo << (FENCE_LOG * k)), 1ull << (FENCE_LOG * k));
+        const uint32_t c = window_count(win, q, t, shift, ng,
+                                        r.g0 + ((uint64_t)lo << (FENCE_LOG * k)),
+                                        1ull << (FENCE_LOG * k));
         if (k == 0) {
-            const uint32_t res = r.g0 + (uint32_t)lo + c;
+            const uint32_t res = r.g0 + lo + c;
             return res < r.gb ? r.gb : res;
         }
         // c == 0 only at the top level: t precedes the segment's first group
         if (c == 0) return r.gb;
         lo = (lo + c - 1) * FENCE_FAN;
-        off -= fence_level_len(cap, k - 1);
+        // level k - 1 < fence_levels(cap) holds cap >> (FENCE_LOG (k - 1)) words
+        off -= (1u << (lg - FENCE_LOG * (k - 1)));
     }
     return r.gb;  // not reached
 }
