@@ -170,6 +170,20 @@ __device__ __forceinline__ StartState walk_start(const WalkArgs& a, const StartP
     return st;
 }
 
+// node2vec's acceptance of candidate dst: u beta_max < beta with beta = 1/p
+// for the previous node, 1 where the window holds the edge prev -> dst, else
+// 1/q. The edge is looked up (a random read of the pair table) only where the
+// answer depends on it: u beta_max between 1 and 1/q (a quarter of the trials
+// for p = 1/2, q = 2, none for q = 1).
+__device__ __forceinline__ bool n2v_accept(const WalkArgs& a, const HopBias& hb, uint64_t x2,
+                                           int32_t prev, int32_t dst) {
+    const double u = unit_closed_open(x2) * hb.beta_max;
+    if (dst == prev) return u < hb.inv_p;
+    const bool adjacent = u < 1.0, apart = u < hb.inv_q;
+    if (adjacent == apart) return adjacent;
+    return adj_has(a.adj_tab, a.adj_mask, prev, dst) ? adjacent : apart;
+}
+
 // The pick of hop `hop` among groups [gc, r.ge) of node cur (previous node
 // prev): the hop bias, or node2vec's rejection loop. Returns false when
 // node2vec exhausts its trials (the walk ends; counted in *cap_count, the
@@ -199,11 +213,7 @@ __device__ __forceinline__ bool hop_pick(const WalkArgs& a, const HopBias& hb, u
         p = pick_node(a.ng, a.n_dst, a.n_ts, gc, r.ge, r.ee, TW_EXPONENTIAL, hb.tau, t_first,
                       r.t_last, d);
         nx = p.dst;
-        double beta;
-        if (nx == prev) beta = hb.inv_p;
-        else if (adj_has(a.adj_tab, a.adj_mask, prev, nx)) beta = 1.0;
-        else beta = hb.inv_q;
-        if (unit_closed_open(d.x2) * hb.beta_max < beta) return true;
+        if (n2v_accept(a, hb, d.x2, prev, nx)) return true;
     }
     atomicAdd(cap_count ? cap_count : &a.err[2], 1u);
     return false;
@@ -330,66 +340,425 @@ struct RowRing {
     }
 };
 
-// One full walk per thread: the full-walk baseline (Sec. "The Full-Walk
-// Baseline"). The walk is bound by dependent random loads, so waves in flight
-// count: the uniform and linear pickers are held to 5 waves per SIMD (they
-// fit 8), the exponential and weight pickers' FP64 code and the mixed-kind
-// instantiation to 4 (no spills; 5 waves spill 14-16 registers there);
-// node2vec (more live state) keeps its own allocation. ROWS: the walk writes
-// its whole output row itself, four slots per store, padding included (rows
-// of a multiple of 4 slots, 16-byte aligned outputs); otherwise the rows were
-// pre-filled with padding and the walk writes the slots it reaches.
-template <int HK, int SK, bool ROWS>
-__global__ void __launch_bounds__(WALK_THREADS)
-__attribute__((amdgpu_waves_per_eu(HK == TW_NODE2VEC ? 1
-                                     : HK < 0 || HK == TW_EXPONENTIAL || HK == TW_WEIGHT
-                                         ? 4
-                                         : 5)))
-k_walk_full(const WalkArgs a) {
-    const int64_t w = (int64_t)blockIdx.x * WALK_THREADS + threadIdx.x;
-    if (w >= a.num_walks) return;
-    const uint64_t id = a.base + (uint64_t)w;
-    int32_t* out_n = a.nodes + w * a.L;
-    int64_t* out_t = a.ts + w * a.L;
-    StartState st = walk_start(a, fixed_start<SK>(start_of(a)), w, id, a.L,
-                               ROWS ? nullptr : out_n, out_t);
-    // ROWS: the row's current four slots in LDS, slot p at [p & 3] (each
-    // thread its own column): registers the FP64 pickers need instead
-    // (exponential walks 4.57 -> 4.39 ms, node2vec 5.49 -> 4.69 ms on the
-    // 100M-edge graph)
-    __shared__ int32_t ring_n[4][WALK_THREADS];
-    __shared__ int64_t ring_t[4][WALK_THREADS];
-    const RowRing ring{ring_n, ring_t, (int)threadIdx.x};
-    if (ROWS) {
-        ring.put(0, st.len >= 1 ? st.first : -1, TS_NONE);
-        ring.put(1, st.len >= 2 ? st.cur : -1, st.len >= 2 ? st.t : TS_NONE);
+// ------------------------------------------------------------- walk blocks
+//
+// A wavefront runs a block of up to 64 x rounds walks, a lane one walk at a
+// time: it takes every start of the block first (all lanes busy), keeps the
+// start states in LDS, and then hops; a lane whose walk has ended takes the
+// block's next start from LDS. Walks of one launch end after very different
+// numbers of hops (7 of 80 slots on average, 20 and more for the longest of
+// 64): with one walk per lane 34 % of the lanes of an instruction did work,
+// 18 % for node2vec, whose rejected trials also held the other lanes back, and
+// each lane padded its own row. The launches are bound by the random lines
+// they read and write (4M exponential walks of length 80 on 100M edges: 5.6
+// TB/s, the copy reaches 4.7), small ones by the chain of dependent loads.
+// One walk per lane -> blocks: that launch 3.75 -> 3.01 ms; 1M uniform walks of
+// 25 slots on an undirected graph 817 -> 731 us (rows of any width no longer
+// pre-filled); 2M node2vec walks 3.71 -> 2.65 ms; 1M weight-based 1.01 -> 0.88
+// ms; 1M backward exponential 1.02 -> 0.69 ms; 10,000 walks 22.1 -> 20.3 us
+// (workgroups of one wavefront; of four: 25.7).
+
+// The walks of a block (uniform over the wavefront): walk j of the block is
+// walk w0 + j stride of its request, with RNG id id0 + j stride.
+struct WalkBlock {
+    int n;
+    int64_t w0, stride;
+    uint64_t id0;
+    int32_t L;  // row width and length limit
+    StartParams sp;
+    HopBias hop;
+    int32_t* nodes;
+    int64_t* ts;
+    int32_t* len;
+    bool vec;              // nodes and ts 16-byte aligned: whole chunks leave as vectors
+    uint32_t* range_flag;  // a start node out of range
+    uint32_t* cap_count;   // walks node2vec's trial cap ended
+};
+
+// LDS of one wavefront: each lane's ring of its walk's current chunk of CH
+// output slots (its own column), and per walk of the block its start state and
+// its length.
+template <int CH>
+struct BlockLds {
+    int32_t* ring_n;
+    int64_t* ring_t;
+    int64_t* t;
+    int32_t *cur, *prev, *len;
+    __device__ BlockLds(unsigned char* base, int rounds) {
+        const int n = 64 * rounds;
+        ring_t = reinterpret_cast<int64_t*>(base);
+        t = ring_t + CH * 64;
+        ring_n = reinterpret_cast<int32_t*>(t + n);
+        cur = ring_n + CH * 64;
+        prev = cur + n;
+        len = prev + n;
     }
-    const HopBias hb = fixed_hop<HK>(a.hop);
-    int32_t len = st.len, cur = st.cur, prev = st.prev;
-    int64_t tcur = st.t;
-    if (len >= 2) {
-        for (uint64_t hop = 1; len < a.L; ++hop) {
-            const NodeRec r = a.rec[cur];
-            if (tcur >= r.t_last) break;  // Gamma_t(cur) is empty
-            const uint32_t gc = fence_search(a.ng, a.fence, r, tcur, nullptr, 0, 0);
-            Pick p;
-            int32_t nx;
-            if (!hop_pick(a, hb, a.seed, r, gc, id, hop, prev, p, nx)) break;
-            if (ROWS) {
-                ring.put(len, nx, p.t);
-                if ((len & 3) == 3) ring.flush(out_n, out_t, len - 3);
-            } else {
-                out_n[len] = nx;
-                out_t[len] = p.t;
+};
+constexpr int block_lds_bytes(int chunk, int rounds) {
+    return chunk * 64 * 12 + 64 * rounds * 20;
+}
+// Chunk and most rounds of a kind's blocks: what LDS holds for 16 wavefronts a
+// compute unit (10 KB each). Chunks of eight slots write whole sectors;
+// node2vec's long and uneven hops gain more from rounds (2M walks of length 40
+// on 50M edges: 2.65 ms with chunks of 4 and 4 rounds, 2.92 with 8 and 2;
+// 4M exponential walks of length 80 on 100M edges 3.19 against 3.05).
+constexpr int block_chunk(int kind) { return kind == TW_NODE2VEC || kind < 0 ? 4 : 8; }
+constexpr int block_max_rounds(int kind) { return kind == TW_NODE2VEC || kind < 0 ? 4 : 2; }
+static_assert(block_lds_bytes(8, 2) <= 10240 && block_lds_bytes(4, 4) <= 10240, "16 a CU");
+
+// idle lanes that make a wavefront end their rows and take new starts while
+// others still hop (1 and 16 measured alike, 32 slower on 1M-walk launches)
+constexpr int BLOCK_REFILL_MIN = 16;
+
+// LDS written by one lane of a wavefront and read by another: in program
+// order for the hardware, so only the compiler has to keep it
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// A lane's output row. The row's slots are grouped in aligned chunks of CH (ph:
+// the row's first slot inside its first chunk), which leave for memory once
+// their last slot is known, as 16-byte stores where four slots belong to the
+// row (chunks of eight: 32 bytes of nodes and a whole 64-byte sector of
+// timestamps at once).
+template <int CH>
+struct RowOut {
+    const WalkBlock& b;
+    const BlockLds<CH>& m;
+    int lane;
+    int j = -1;  // the walk of the block
+    int ph = 0;
+    __device__ __forceinline__ int64_t first() const { return (b.w0 + j * b.stride) * b.L; }
+    __device__ __forceinline__ void open(int jj) {
+        j = jj;
+        ph = (int)(first() & (CH - 1));
+    }
+    // The row's slots [from, to) of the chunk at slot q (a multiple of CH); the
+    // slots from `known` on are padding.
+    __device__ __forceinline__ void store(int64_t q, int from, int to, int known) const {
+        const int64_t at = first() - ph + q;
+#pragma unroll
+        for (int k0 = 0; k0 < CH; k0 += 4) {
+            int32_t v[4];
+            int64_t x[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                v[i] = k0 + i < known ? m.ring_n[(k0 + i) * 64 + lane] : -1;
+                x[i] = k0 + i < known ? m.ring_t[(k0 + i) * 64 + lane] : TS_NONE;
             }
-            ++len;
-            prev = cur;
-            cur = nx;
-            tcur = p.t;
+            int32_t* n = b.nodes + at + k0;
+            int64_t* t = b.ts + at + k0;
+            if (b.vec && from <= k0 && k0 + 4 <= to) {
+                *reinterpret_cast<int4*>(n) = make_int4(v[0], v[1], v[2], v[3]);
+                *reinterpret_cast<longlong2*>(t) = make_longlong2(x[0], x[1]);
+                *reinterpret_cast<longlong2*>(t + 2) = make_longlong2(x[2], x[3]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (k0 + i >= from && k0 + i < to) {
+                        n[i] = v[i];
+                        t[i] = x[i];
+                    }
+            }
         }
     }
-    if (ROWS) ring.finish(out_n, out_t, len, a.L);
-    finish_walk(a, w, len);
+    __device__ __forceinline__ void push(int32_t p, int32_t v, int64_t t) const {
+        const int64_t q = (int64_t)ph + p;
+        const int r = (int)(q & (CH - 1));
+        m.ring_n[r * 64 + lane] = v;
+        m.ring_t[r * 64 + lane] = t;
+        if (r == CH - 1) store(q - r, q - r < ph ? ph : 0, CH, CH);
+    }
+    // ends a row of len slots: the chunk of the last slot is completed with
+    // padding up to the row's end (the padding passes write the rest)
+    __device__ __forceinline__ void finish(int32_t len) const {
+        const int64_t q = (int64_t)ph + len;
+        const int r = (int)(q & (CH - 1));
+        if (len == 0 || r == 0) return;
+        const int64_t c = q - r, end = (int64_t)ph + b.L - c;
+        store(c, c < ph ? ph : 0, end < CH ? (int)end : CH, r);
+    }
+    // first slot of a row that finish(len) leaves to the padding passes
+    __device__ static __forceinline__ int32_t written(int64_t row0, int32_t len, int32_t width) {
+        if (len == 0) return 0;
+        const int64_t ph = row0 & (CH - 1);
+        const int64_t at = ((ph + len + CH - 1) & ~(int64_t)(CH - 1)) - ph;
+        return at < width ? (int32_t)at : width;
+    }
+};
+
+// Padding of one row from slot `at` to its end by `lanes` lanes (this one
+// is lane `sub`): consecutive lanes write consecutive 16 bytes.
+__device__ __forceinline__ void pad_row(int32_t* __restrict__ nodes, int64_t* __restrict__ ts,
+                                        int64_t row0, int64_t at, int32_t width, bool vec, int sub,
+                                        int lanes) {
+    const int64_t b = row0 + at, e = row0 + width;
+    if (!vec) {
+        for (int64_t s = b + sub; s < e; s += lanes) {
+            nodes[s] = -1;
+            ts[s] = TS_NONE;
+        }
+        return;
+    }
+    const int64_t vb = (b + 3) & ~3ll, ve = e & ~3ll;  // whole chunks
+    const int64_t head = vb < e ? vb : e;
+    if (b + sub < head) {
+        nodes[b + sub] = -1;
+        ts[b + sub] = TS_NONE;
+    }
+    for (int64_t s = vb + 4 * sub; s < ve; s += 4 * lanes)
+        *reinterpret_cast<int4*>(nodes + s) = make_int4(-1, -1, -1, -1);
+    for (int64_t s = vb + 2 * sub; s < ve; s += 2 * lanes)
+        *reinterpret_cast<longlong2*>(ts + s) = make_longlong2(TS_NONE, TS_NONE);
+    if (ve >= vb && ve + sub < e) {
+        nodes[ve + sub] = -1;
+        ts[ve + sub] = TS_NONE;
+    }
+}
+
+// Padding of a block of n rows of L slots each from slot s0 of the outputs,
+// row r from its slot at[r] on: groups of four slots of the whole block over
+// consecutive lanes, so a store instruction covers 1 KB without a gap. The
+// row of a slot comes from a multiplication, exact for L < 4096.
+constexpr int PAD_FLAT_MIN_L = 4, PAD_FLAT_MAX_L = 4096;
+__device__ __forceinline__ void pad_rows_flat(int32_t* __restrict__ nodes, int64_t* __restrict__ ts,
+                                              int64_t s0, int n, int32_t L, const int32_t* at,
+                                              int lane) {
+    const uint32_t inv = 0xFFFFFFFFu / (uint32_t)L + 1u;  // ceil(2^32 / L)
+    const int ph = (int)(s0 & 3);
+    int32_t* on = nodes + (s0 - ph);
+    int64_t* ot = ts + (s0 - ph);
+    const int quads = (ph + n * L + 3) >> 2;
+    // whether quad c lies in one row; its first own slot's row and place there
+    auto place = [&](int c, int& r, int& p) {
+        const int x = 4 * c - ph, y = x < 0 ? 0 : x;
+        r = (int)__umulhi((uint32_t)y, inv);
+        p = y - r * L;
+        return x >= 0 && p + 4 <= L;
+    };
+    // (a row's `at` is a multiple of four from the aligned start, or its end)
+#pragma unroll 2
+    for (int c = lane; c < quads; c += 64) {
+        int r, p;
+        if (place(c, r, p)) {
+            if (p >= at[r]) *reinterpret_cast<int4*>(on + 4 * c) = make_int4(-1, -1, -1, -1);
+        } else {  // a quad that ends one row and begins the next (or an end of the block)
+            for (int q = 4 * c < ph ? ph : 4 * c; q < 4 * c + 4 && r < n; ++q) {
+                if (p >= at[r]) {
+                    on[q] = -1;
+                    ot[q] = TS_NONE;
+                }
+                if (++p == L) {
+                    ++r;
+                    p = 0;
+                }
+            }
+        }
+    }
+#pragma unroll 4
+    for (int h = lane; h < 2 * quads; h += 64) {
+        int r, p;
+        if (place(h >> 1, r, p) && p >= at[r])
+            *reinterpret_cast<longlong2*>(ot + 2 * h) = make_longlong2(TS_NONE, TS_NONE);
+    }
+}
+
+// The candidates of a hop: groups [c0, c1) of a node with edges ending at
+// end, their first and last timestamps, the node's first live group.
+struct Candidates {
+    uint32_t c0, c1, end, gb;
+    int64_t t_lo, t_hi;
+};
+
+// Gamma_t of the node of record r: forward the groups after t, backward (on
+// the in-view) those before t; false when there is none. rate: the pick reads
+// the first candidate's timestamp.
+template <bool REV>
+__device__ __forceinline__ bool candidates(const WalkArgs& a, const NodeRec& r, int64_t t,
+                                           bool rate, Candidates& c) {
+    c.gb = r.gb;
+    if (!REV) {
+        if (t >= r.t_last) return false;
+        c.c0 = fence_search(a.ng, a.fence, r, t, nullptr, 0, 0);
+        c.c1 = r.ge;
+        c.end = r.ee;
+        c.t_lo = rate ? group_ts(a.ng, a.fence, r, c.c0) : 0;
+        c.t_hi = r.t_last;
+        return true;
+    }
+    if (r.gb == r.ge) return false;
+    // the first group at or after t (first with a timestamp > t - 1)
+    const uint32_t hi = t - 1 >= r.t_last
+                            ? r.ge
+                            : fence_search(a.ng, a.fence, r, t - 1, nullptr, 0, 0);
+    if (hi == r.gb) return false;
+    c.c0 = r.gb;
+    c.c1 = hi;
+    c.end = hi < r.ge ? a.ng[hi].first : r.ee;
+    c.t_lo = rate ? group_ts(a.ng, a.fence, r, r.gb) : 0;
+    c.t_hi = rate ? group_ts(a.ng, a.fence, r, hi - 1) : 0;
+    return true;
+}
+
+// keeps a value's computation above this point (a draw made while a load
+// it does not need is in flight)
+__device__ __forceinline__ void computed_here(uint64_t& x) { asm volatile("" : "+v"(x)); }
+
+// The walks of block b, by one wavefront. Each round of the loop is one
+// attempt of a hop per lane: node2vec's rejected trials are attempts of their
+// own, so a lane whose trial was accepted goes on to its next hop while
+// others try again.
+template <int HK, int SK, bool REV, int CH>
+__device__ __forceinline__ void walk_block(const WalkArgs& a, const WalkBlock& b,
+                                           const BlockLds<CH>& m) {
+    const int lane = threadIdx.x & 63;
+    const HopBias hb = fixed_hop<HK>(b.hop);
+    const StartParams sp = fixed_start<SK>(b.sp);
+    const bool n2v = hb.kind == TW_NODE2VEC;
+#pragma unroll 1
+    for (int j = lane; j < b.n; j += 64) {
+        const int64_t w = b.w0 + j * b.stride;
+        const StartState st = walk_start(a, sp, w, b.id0 + (uint64_t)(j * b.stride), b.L, nullptr,
+                                         nullptr, REV, b.range_flag);
+        m.prev[j] = st.first;
+        m.cur[j] = st.cur;
+        m.t[j] = st.t;
+        m.len[j] = st.len;
+    }
+    wave_lds_fence();
+
+    RowOut<CH> row{b, m, lane};
+    const int32_t& j = row.j;  // this lane's walk of the block (-1: none)
+    bool active = false;       // the walk goes on
+    int next = 0;
+    uint32_t trial = 0;
+    int32_t len = 0, cur = 0, prev = 0;
+    int64_t t = 0;
+    Candidates c{};
+    ExpLaw law{};
+    while (true) {
+        // Lanes whose walk has ended keep its last chunk in LDS until enough
+        // of them wait (or no walk goes on): ending rows and taking starts
+        // costs the whole wavefront the same for one lane as for many.
+        const uint64_t busy = __ballot(active);
+        if (busy == 0 || (next < b.n && __popcll(busy) <= 64 - BLOCK_REFILL_MIN)) {
+            if (!active) {
+                if (j >= 0) {
+                    row.finish(len);
+                    m.len[j] = len;
+                }
+                const int at = next + __popcll(~busy & ((1ull << lane) - 1));
+                if (at < b.n) {
+                    row.open(at);
+                    prev = m.prev[at];
+                    cur = m.cur[at];
+                    t = m.t[at];
+                    len = m.len[at];
+                    trial = 0;
+                    if (len >= 1) row.push(0, prev, TS_NONE);
+                    if (len >= 2) row.push(1, cur, t);
+                    active = len >= 2 && len < b.L;
+                } else {
+                    row.j = -1;
+                }
+            }
+            if (busy == 0 && next >= b.n) break;  // every row has ended
+            next += 64 - __popcll(busy);
+        }
+        if (active) {
+            const bool fresh = !n2v || trial == 0;
+            NodeRec r;
+            if (fresh) r = a.rec[cur];
+            // hop len - 1 of the walk
+            Draw d = philox(b.id0 + (uint64_t)(j * b.stride), (uint64_t)(len - 1), trial, sp.seed);
+            computed_here(d.x0);
+            bool live = true;
+            if (fresh) {
+                live = candidates<REV>(a, r, t, reads_first_ts(hb.kind), c);
+                if (n2v && live)
+                    law = exp_law(c.c1 - c.c0, exp_lambda(c.t_lo, c.t_hi, c.c1 - c.c0, hb.tau));
+            }
+            if (!live) {
+                active = false;
+            } else {
+                Pick p;
+                bool take = true;
+                if (!REV && hb.kind == TW_WEIGHT) {
+                    p = pick_weight(a.ng, a.n_dst, a.cw, c.gb, c.c0, c.c1, c.end,
+                                    hb.tau > 0.0 ? hb.tau : 1.0, group_ts(a.ng, a.fence, r, c.c0),
+                                    c.t_hi, d);
+                } else if (n2v) {
+                    const uint32_t i = exp_draw(law, d.x0);
+                    p = edge_of_group(a.ng, a.n_dst, c.c1, c.end, REV ? c.c1 - 1 - i : c.c0 + i, d,
+                                      REV);
+                    // the edge prev -> candidate (backward: candidate -> prev
+                    // of the graph, which is prev -> candidate of the in-view)
+                    take = n2v_accept(a, hb, d.x2, prev, p.dst);
+                } else {
+                    p = pick_node(a.ng, a.n_dst, a.n_ts, c.c0, c.c1, c.end, hb.kind, hb.tau, c.t_lo,
+                                  c.t_hi, d, REV);
+                }
+                if (take) {
+                    row.push(len, p.dst, p.t);
+                    ++len;
+                    trial = 0;
+                    prev = cur;
+                    cur = p.dst;
+                    t = p.t;
+                    active = len < b.L;
+                } else if (++trial == N2V_MAX_TRIALS) {
+                    atomicAdd(b.cap_count, 1u);
+                    active = false;
+                }
+            }
+        }
+    }
+    wave_lds_fence();
+    // lengths out; from here m.len holds each row's first slot left to pad
+    for (int k = lane; k < b.n; k += 64) {
+        const int64_t w = b.w0 + k * b.stride;
+        const int32_t l = m.len[k];
+        b.len[w] = l;
+        m.len[k] = RowOut<CH>::written(w * (int64_t)b.L, l, b.L);
+    }
+    wave_lds_fence();
+    if (b.vec && b.stride == 1 && b.L >= PAD_FLAT_MIN_L && b.L < PAD_FLAT_MAX_L) {
+        pad_rows_flat(b.nodes, b.ts, b.w0 * (int64_t)b.L, b.n, b.L, m.len, lane);
+        return;
+    }
+    // 16 lanes a row
+    const int sub = lane & 15;
+    for (int k = lane >> 4; k < b.n; k += 4)
+        pad_row(b.nodes, b.ts, (b.w0 + k * b.stride) * (int64_t)b.L, m.len[k], b.L, b.vec, sub, 16);
+}
+
+// The full-walk dispatch (Sec. "The Full-Walk Baseline"), forward and (REV, on
+// the in-view) backward: contiguous blocks of 64 x rounds walks, a workgroup of
+// one wavefront each, held to 4 wavefronts a SIMD (what the blocks' LDS allows).
+template <int HK, int SK, bool REV>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4)))
+k_walk_full(const WalkArgs a, int rounds) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int per = 64 * rounds;
+    WalkBlock b;
+    b.w0 = (int64_t)blockIdx.x * per;
+    b.n = (int)std::min<int64_t>(per, a.num_walks - b.w0);
+    b.stride = 1;
+    b.id0 = a.base + (uint64_t)b.w0;
+    b.L = a.L;
+    b.sp = start_of(a);
+    b.hop = a.hop;
+    b.nodes = a.nodes;
+    b.ts = a.ts;
+    b.len = a.len;
+    b.vec = (((uintptr_t)a.nodes | (uintptr_t)a.ts) & 15) == 0;
+    b.range_flag = &a.err[0];
+    b.cap_count = &a.err[2];
+    constexpr int CH = block_chunk(HK);
+    walk_block<HK, SK, REV, CH>(a, b,
+                                BlockLds<CH>(lds, rounds));
 }
 
 // Backward walks (Gamma-_t(v): in-edges of v with t' < t, the backward case
@@ -417,49 +786,10 @@ __device__ __forceinline__ bool back_pick(const WalkArgs& a, const HopBias& hb, 
         p = pick_node(a.ng, a.n_dst, a.n_ts, r.gb, hi, end, TW_EXPONENTIAL, hb.tau, t_lo, t_hi,
                       d, true);
         nx = p.dst;
-        double beta;
-        if (nx == prev) beta = hb.inv_p;
-        else if (adj_has(a.adj_tab, a.adj_mask, prev, nx)) beta = 1.0;
-        else beta = hb.inv_q;
-        if (unit_closed_open(d.x2) * hb.beta_max < beta) return true;
+        if (n2v_accept(a, hb, d.x2, prev, nx)) return true;
     }
     atomicAdd(cap_count ? cap_count : &a.err[2], 1u);
     return false;
-}
-
-// One backward walk per thread (full-walk form).
-template <int HK, int SK>
-__global__ void __launch_bounds__(WALK_THREADS) k_walk_back(const WalkArgs a) {
-    const int64_t w = (int64_t)blockIdx.x * WALK_THREADS + threadIdx.x;
-    if (w >= a.num_walks) return;
-    const uint64_t id = a.base + (uint64_t)w;
-    int32_t* out_n = a.nodes + w * a.L;
-    int64_t* out_t = a.ts + w * a.L;
-    StartState st = walk_start(a, fixed_start<SK>(start_of(a)), w, id, a.L, out_n, out_t, true);
-    const HopBias hb = fixed_hop<HK>(a.hop);
-    int32_t len = st.len, cur = st.cur, prev = st.prev;
-    int64_t tcur = st.t;
-    if (len >= 2) {
-        for (uint64_t hop = 1; len < a.L; ++hop) {
-            const NodeRec r = a.rec[cur];
-            if (r.gb == r.ge) break;  // no in-edge at all
-            // the first group at or after tcur (first with a timestamp > tcur - 1)
-            const uint32_t hi = tcur - 1 >= r.t_last
-                                    ? r.ge
-                                    : fence_search(a.ng, a.fence, r, tcur - 1, nullptr, 0, 0);
-            if (hi == r.gb) break;  // Gamma- is empty
-            Pick p;
-            int32_t nx;
-            if (!back_pick(a, hb, a.seed, r, hi, id, hop, prev, p, nx)) break;
-            out_n[len] = nx;
-            out_t[len] = p.t;
-            ++len;
-            prev = cur;
-            cur = nx;
-            tcur = p.t;
-        }
-    }
-    finish_walk(a, w, len);
 }
 
 // ----------------------------------------------------------------- queue
@@ -1386,25 +1716,40 @@ tw_status queue_hops(tw_graph* g, const WalkArgs& a, int bpc, Error& err) {
 }
 
 
-// run the walks of `a` under a dispatch; the output rows are padded first
-// unless the walk kernel writes them whole
-tw_status run_dispatch(tw_graph* g, const WalkArgs& a, int dispatch, int bpc, Error& err) {
-    if ((dispatch != TW_DISPATCH_FULL_WALK && dispatch != TW_DISPATCH_QUEUE) || !own_rows(a))
-        launch_fill(g, a.nodes, a.ts, a.num_walks * (int64_t)a.L);
-    if (dispatch == TW_DISPATCH_COOP) return coop_walks(g, a, err);
-    if (dispatch == TW_DISPATCH_QUEUE) return queue_hops(g, a, bpc, err);
-    const bool rows = own_rows(a);
+// Rounds of a block (64 walks each): more rounds keep more lanes busy, as
+// long as the launch still fills the chip (16 wavefronts a compute unit): a
+// 1M-walk launch is 8,192 blocks of 2 rounds for 4,096 places (weight-based
+// walks 0.88 ms, with 3 rounds 0.99).
+int block_rounds(const tw_graph* g, int64_t walks, int kind) {
+    const int64_t chip = (int64_t)g->cu_count * 16 * 64;
+    return (int)std::clamp<int64_t>(walks / chip, 1, block_max_rounds(kind));
+}
+
+// the full-walk kernel; it writes whole rows, padding included
+tw_status full_walks(tw_graph* g, const WalkArgs& a, bool rev, Error& err) {
+    if (queue_shape(g, err) != TW_OK) return err.code;
+    const int rounds = block_rounds(g, a.num_walks, a.hop.kind);
+    const dim3 grid((unsigned)ceil_div(a.num_walks, (int64_t)64 * rounds));
+    const size_t lds = (size_t)block_lds_bytes(block_chunk(a.hop.kind), rounds);
     with_kinds(a.hop.kind, a.start_kind, [&](auto h, auto st) {
-        const dim3 grid((unsigned)ceil_div(a.num_walks, WALK_THREADS));
-        if (rows)
-            hipLaunchKernelGGL((k_walk_full<decltype(h)::value, decltype(st)::value, true>), grid,
-                               dim3(WALK_THREADS), 0, g->stream, a);
-        else
-            hipLaunchKernelGGL((k_walk_full<decltype(h)::value, decltype(st)::value, false>),
-                               grid, dim3(WALK_THREADS), 0, g->stream, a);
+        with_direction(rev, decltype(h)::value, [&](auto r) {
+            hipLaunchKernelGGL((k_walk_full<decltype(h)::value, decltype(st)::value,
+                                            decltype(r)::value>),
+                               grid, dim3(64), lds, g->stream, a, rounds);
+        });
     });
     TW_HIP(hipGetLastError());
     return TW_OK;
+}
+
+// run the walks of `a` under a dispatch; the output rows are padded first
+// unless the walk kernel writes them whole
+tw_status run_dispatch(tw_graph* g, const WalkArgs& a, int dispatch, int bpc, Error& err) {
+    if (dispatch == TW_DISPATCH_FULL_WALK) return full_walks(g, a, false, err);
+    if (dispatch != TW_DISPATCH_QUEUE || !own_rows(a))
+        launch_fill(g, a.nodes, a.ts, a.num_walks * (int64_t)a.L);
+    if (dispatch == TW_DISPATCH_COOP) return coop_walks(g, a, err);
+    return queue_hops(g, a, bpc, err);
 }
 
 tw_status prepare_plain(tw_graph* g, const tw_walk_params* p, int32_t* nodes, int64_t* ts,
@@ -1453,22 +1798,16 @@ tw_status sample_backward(tw_graph* g, const tw_walk_params* p, int32_t* nodes, 
     WalkArgs a;
     if (prepare_plain(b, p, nodes, ts, len, a, err) != TW_OK) return err.code;
     if (p->num_walks == 0) return TW_OK;
-    launch_fill(b, nodes, ts, p->num_walks * (int64_t)p->max_len);
     if (p->dispatch == TW_DISPATCH_QUEUE) {
         // the work queue with the one hop bias
+        launch_fill(b, nodes, ts, p->num_walks * (int64_t)p->max_len);
         QueueArgs q{};
         q.n_bias = 1;
         q.bias[0] = a.hop;
         q.out_slots = p->num_walks * (int64_t)p->max_len;
         return queue_walks(b, a, q, g->auto_bpc, err, true);
     }
-    const dim3 grid((unsigned)ceil_div(p->num_walks, WALK_THREADS));
-    with_kinds(a.hop.kind, a.start_kind, [&](auto h, auto sk) {
-        hipLaunchKernelGGL((k_walk_back<decltype(h)::value, decltype(sk)::value>), grid,
-                           dim3(WALK_THREADS), 0, b->stream, a);
-    });
-    TW_HIP(hipGetLastError());
-    return TW_OK;
+    return full_walks(b, a, true, err);
 }
 
 tw_status sample_walks(tw_graph* g, const tw_walk_params* p, int32_t* nodes, int64_t* ts,
@@ -1741,21 +2080,14 @@ tw_status serve_launch(tw_graph* g, const ServeReq* reqs, int n, void* d_table, 
         if (fill_args(g, q.count, q.max_len, q.start, q.start_mode, q.start_nodes, q.seed, q.base,
                       q.hop.kind == TW_NODE2VEC, NAN, q.nodes, q.ts, q.len, a, err) != TW_OK)
             return err.code;
-        if (own_rows(a)) {
-            a.hop = make_hop_bias(q.hop);
-            a.err = d_err;  // [0] start node out of range, [2] trial-cap hits
-            hipLaunchKernelGGL(k_err_words, dim3(1), dim3(64), 0, g->stream, d_err, 0);
-            const dim3 grid((unsigned)ceil_div(q.count, WALK_THREADS));
-            with_kinds(a.hop.kind, a.start_kind, [&](auto h, auto st) {
-                hipLaunchKernelGGL((k_walk_full<decltype(h)::value, decltype(st)::value, true>),
-                                   grid, dim3(WALK_THREADS), 0, g->stream, a);
-            });
-            hipLaunchKernelGGL(k_err_words, dim3(1), dim3(64), 0, g->stream, d_err, 1);
-            hipLaunchKernelGGL(k_sum_hops, dim3(1024), dim3(256), 0, g->stream, q.len, q.count,
-                               d_hops);
-            TW_HIP(hipGetLastError());
-            return TW_OK;
-        }
+        a.hop = make_hop_bias(q.hop);
+        a.err = d_err;  // [0] start node out of range, [2] trial-cap hits
+        hipLaunchKernelGGL(k_err_words, dim3(1), dim3(64), 0, g->stream, d_err, 0);
+        if (full_walks(g, a, false, err) != TW_OK) return err.code;
+        hipLaunchKernelGGL(k_err_words, dim3(1), dim3(64), 0, g->stream, d_err, 1);
+        hipLaunchKernelGGL(k_sum_hops, dim3(1024), dim3(256), 0, g->stream, q.len, q.count, d_hops);
+        TW_HIP(hipGetLastError());
+        return TW_OK;
     }
     bool n2v = false;
     double wtau = NAN;  // the weight-based requests' time scale: one per launch

@@ -74,20 +74,41 @@ __device__ __forceinline__ double exp_lambda(int64_t t_first, int64_t t_last, ui
     return (double)(t_last - t_first) / ((double)(n - 1) * tau);
 }
 
-// Eq. (3) as the exact inverse CDF of P(i) ~ exp(lambda i), i in [0, n)
-__device__ __forceinline__ uint32_t pick_exponential(uint32_t n, double lam, uint64_t x) {
-    if (n <= 1) return 0;
-    double u = unit_open(x);
-    double ln = lam * (double)n;
+// Eq. (3) as the exact inverse CDF of P(i) ~ exp(lambda i), i in [0, n): the
+// part of it that does not depend on the draw (node2vec draws several times
+// from one law), and the draw.
+struct ExpLaw {
+    uint32_t n;
+    double lam;
+    bool flat;  // lambda n <= 1
+    double e;   // expm1(lambda n) when flat, else exp(-lambda n)
+};
+
+__device__ __forceinline__ ExpLaw exp_law(uint32_t n, double lam) {
+    ExpLaw w{n, lam, true, 0.0};
+    if (n <= 1) return w;
+    const double ln = lam * (double)n;
+    w.flat = ln <= 1.0;
+    w.e = w.flat ? expm1(ln) : exp(-ln);
+    return w;
+}
+
+__device__ __forceinline__ uint32_t exp_draw(const ExpLaw& w, uint64_t x) {
+    if (w.n <= 1) return 0;
+    const double u = unit_open(x);
     double xi;
-    if (ln <= 1.0)
-        xi = log1p(u * expm1(ln)) / lam;
+    if (w.flat)
+        xi = log1p(u * w.e) / w.lam;
     else
-        xi = (double)n + log(u + (1.0 - u) * exp(-ln)) / lam;
-    double f = floor(xi);
+        xi = (double)w.n + log(u + (1.0 - u) * w.e) / w.lam;
+    const double f = floor(xi);
     if (!(f >= 0.0)) return 0;
-    if (f >= (double)(n - 1)) return n - 1;
+    if (f >= (double)(w.n - 1)) return w.n - 1;
     return (uint32_t)f;
+}
+
+__device__ __forceinline__ uint32_t pick_exponential(uint32_t n, double lam, uint64_t x) {
+    return exp_draw(exp_law(n, lam), x);
 }
 
 // count of the groups [lo, hi) (timestamps ascending) whose timestamp is
@@ -261,6 +282,18 @@ struct Pick {
     int64_t t;
 };
 
+// an edge of group k (of groups ending at ge, edges ending at end): the draw's
+// uniform pick inside the group
+__device__ __forceinline__ Pick edge_of_group(const GroupRec* __restrict__ ng,
+                                              const int32_t* __restrict__ n_dst, uint32_t ge,
+                                              uint32_t end, uint32_t k, const Draw& d, bool rev) {
+    const GroupRec a = ng[k];
+    if (a.dst < 0) return Pick{a.dst & 0x7fffffff, a.ts};  // a one-edge group
+    const uint32_t size = (k + 1 < ge ? ng[k + 1].first : end) - a.first;
+    const uint32_t j = (uint32_t)scale_u64(d.x1, size);
+    return Pick{n_dst[a.first + (rev ? size - 1 - j : j)], a.ts};
+}
+
 // rev: a backward walk lists the candidates in reverse, so every index i
 // among n (the edge, the group, the edge inside the group) becomes n - 1 - i.
 // t_first and t_last are the timestamps of the first and the last candidate
@@ -279,12 +312,7 @@ __device__ __forceinline__ Pick pick_node(const GroupRec* __restrict__ ng,
     }
     const uint32_t n = ge - gc;
     const uint32_t i = pick_group(n, kind, tau, n > 1 ? t_first : 0, t_last, d.x0);
-    const uint32_t k = rev ? ge - 1 - i : gc + i;
-    const GroupRec a = ng[k];
-    if (a.dst < 0) return Pick{a.dst & 0x7fffffff, a.ts};  // a one-edge group
-    const uint32_t size = (k + 1 < ge ? ng[k + 1].first : end) - a.first;
-    const uint32_t j = (uint32_t)scale_u64(d.x1, size);
-    return Pick{n_dst[a.first + (rev ? size - 1 - j : j)], a.ts};
+    return edge_of_group(ng, n_dst, ge, end, rev ? ge - 1 - i : gc + i, d, rev);
 }
 
 // The weight-based pick (Sec. "Temporal Bias Sampling") among groups
