@@ -376,18 +376,13 @@ tw_status tw_autotune(tw_graph* g, const tw_walk_params* params, int64_t sample_
 #define TW_NOALLOC_MAX_WALKS 262144
 
 /*
- * The walks of tw_sample_walks with TW_DISPATCH_QUEUE (the same results),
- * with no device allocation, free or memset: the call's lists (live walks
- * and their previous nodes, alive flags and their scan, the work-queue
- * counters; 44 bytes a walk, 11.5 MB in all) live in one array that the
- * library holds on every device it runs on until the process ends, set up by
- * tw_create. Every clearing is a kernel, so the call can be captured in a
- * HIP graph. Arguments and outputs as tw_sample_walks; params->dispatch is
- * ignored. Stream-ordered, no synchronisation.
- * All calls on one device share the array and each call's kernels consume
- * what its own earlier kernels wrote there: calls that overlap on one device
- * (other streams, other host threads, replays of captured graphs running
- * concurrently) race and give wrong walks. Serialise them.
+ * The walks of tw_sample_walks (the same results), with no device
+ * allocation, free or memset: one kernel that keeps a walk's state in
+ * registers and on-chip memory, so the call can be captured in a HIP graph.
+ * Arguments and outputs as tw_sample_walks; params->dispatch is ignored.
+ * Stream-ordered, no synchronisation; calls on several graphs or streams, and
+ * replays of captured calls, may overlap (one graph handle still belongs to
+ * one host thread at a time).
  * Returns TW_EINVAL, nothing enqueued, for num_walks > TW_NOALLOC_MAX_WALKS,
  * backward walks, a TW_WEIGHT hop bias (its weights are built lazily), a
  * graph that has not ingested yet, a TW_NODE2VEC hop bias while the node2vec

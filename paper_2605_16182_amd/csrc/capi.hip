@@ -86,12 +86,6 @@ tw_status tw_create(const tw_config* cfg, tw_graph** out) {
             delete g;
             return fail(TW_EDEVICE, "tw_create: no HIP device");
         }
-        // the device array of tw_sample_walks_noalloc, with the device current
-        tw::Error e{TW_OK, ""};
-        if (tw::noalloc_setup(g->device, e) != TW_OK) {
-            delete g;
-            return report(e.code, e);
-        }
         *out = g;
         return TW_OK;
     });

@@ -641,13 +641,6 @@ hipError_t scan_exclusive_u32(const uint32_t* in, uint32_t* out, int64_t n, uint
     return scan_exclusive<uint32_t, uint32_t>(in, out, n, total, ws.scan_part, s);
 }
 
-int64_t scan_parts_u32(int64_t n) { return ceil_div(std::max<int64_t>(n, 1), SCAN_TILE) + 1; }
-
-hipError_t scan_exclusive_u32_into(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* total,
-                                   uint32_t* part, hipStream_t s) {
-    return scan_core<uint32_t, uint32_t>(in, out, n, total, part, s);
-}
-
 hipError_t scan_exclusive_u32x4(const uint32_t* const in[4], uint32_t* const out[4],
                                 uint32_t* const total[4], int64_t n, Workspace& ws,
                                 hipStream_t s, const uint32_t* n_dev) {

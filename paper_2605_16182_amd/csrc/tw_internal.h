@@ -229,12 +229,6 @@ struct Workspace {
 hipError_t scan_exclusive_u32(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* total,
                               Workspace& ws, hipStream_t s);
 
-// The same scan with caller-provided room for its partial sums (at least
-// scan_parts_u32(n) words at part): it allocates nothing.
-int64_t scan_parts_u32(int64_t n);
-hipError_t scan_exclusive_u32_into(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* total,
-                                   uint32_t* part, hipStream_t s);
-
 // Four exclusive u32 scans of n elements at once (in[k] and out[k] may
 // alias); total[k] (device, nullable) receives the sum of array k.
 // n_dev (nullable): the arrays hold n_dev[0] + n_dev[1] elements, counted on
@@ -526,9 +520,6 @@ tw_status autotune(tw_graph* g, const tw_walk_params* p, int64_t sample, int32_t
 tw_tuning get_tuning(const tw_graph* g);
 void set_tuning_fields(tw_graph* g, const tw_tuning& t);
 tw_status set_tuning(tw_graph* g, const tw_tuning* t, Error& err);
-// allocation-free walks: set-up once per device (device current), the call
-tw_status noalloc_setup(int device, Error& err);
-int64_t noalloc_scratch_bytes();
 tw_status sample_walks_noalloc(tw_graph* g, const tw_walk_params* p, int32_t* nodes, int64_t* ts,
                                int32_t* len, Error& err);
 

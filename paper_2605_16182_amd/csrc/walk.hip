@@ -4,7 +4,6 @@
 // same walks.
 #include <algorithm>
 #include <cmath>
-#include <mutex>
 #include <type_traits>
 #include <vector>
 
@@ -1639,42 +1638,41 @@ bool own_rows(const WalkArgs& a) {
            (reinterpret_cast<uintptr_t>(a.ts) & 15) == 0;
 }
 
-// Per-call lists of the queue dispatch of plain walks: the walks alive after
-// their start (current node, walk, time) before and after compaction, each
-// walk's previous node, the alive flags and their scan, the live count, the
-// scan's partial sums (scan_parts_u32(walks) words) and the queue counters.
-struct HopLists {
-    Live live, next;
-    int32_t* prev;
-    uint32_t* flags;
-    uint32_t* pos;
-    uint32_t* n_live;
-    uint32_t* scan_part;
-    unsigned long long* counters;
-};
-
 // The queue dispatch of plain walks: every start in one pass (as the
 // cooperative dispatch starts), the live walks compacted, then one
-// persistent launch of k_walk_hops over them. Allocates nothing.
-tw_status queue_hops_in(tw_graph* g, const WalkArgs& a, int bpc, const HopLists& h,
-                        Error& err) {
+// persistent launch of k_walk_hops over them. The lists (the walks alive
+// after their start before and after compaction, each walk's previous node,
+// the alive flags and their scan) are graph buffers, grown as needed.
+tw_status queue_hops(tw_graph* g, const WalkArgs& a, int bpc, Error& err) {
     hipStream_t s = g->stream;
     const int64_t W = a.num_walks;
     if (queue_shape(g, err) != TW_OK) return err.code;
+    DevBuf* bufs32[] = {&g->c_node0, &g->c_walk0, &g->c_node2, &g->c_walk2, &g->c_flags,
+                        &g->c_pos, &g->c_prev};
+    for (DevBuf* b : bufs32) TW_HIP(ensure(*b, sizeof(uint32_t) * W, s));
+    TW_HIP(ensure(g->c_t0, sizeof(uint64_t) * W, s));
+    TW_HIP(ensure(g->c_t2, sizeof(uint64_t) * W, s));
+    TW_HIP(ensure(g->wq, sizeof(unsigned long long) * QUEUE_SLICES, s));
+    const Live live{g->c_node0.as<uint32_t>(), g->c_walk0.as<uint32_t>(), g->c_t0.as<uint64_t>()};
+    const Live next{g->c_node2.as<uint32_t>(), g->c_walk2.as<uint32_t>(), g->c_t2.as<uint64_t>()};
+    int32_t* prev = g->c_prev.as<int32_t>();
+    uint32_t* flags = g->c_flags.as<uint32_t>();
+    uint32_t* pos = g->c_pos.as<uint32_t>();
+    uint32_t* n_live = g->scal.as<uint32_t>() + SLOT_U32_N_LIVE;
+    unsigned long long* counters = g->wq.as<unsigned long long>();
     const dim3 wgrid((unsigned)ceil_div(W, WALK_THREADS));
     const bool rows = own_rows(a);
     with_kinds(-1, a.start_kind, [&](auto, auto sk) {
         if (rows)
             hipLaunchKernelGGL((k_coop_start<decltype(sk)::value, true>), wgrid,
-                               dim3(WALK_THREADS), 0, s, a, h.next, h.prev, h.flags);
+                               dim3(WALK_THREADS), 0, s, a, next, prev, flags);
         else
             hipLaunchKernelGGL((k_coop_start<decltype(sk)::value, false>), wgrid,
-                               dim3(WALK_THREADS), 0, s, a, h.next, h.prev, h.flags);
+                               dim3(WALK_THREADS), 0, s, a, next, prev, flags);
     });
-    TW_HIP(scan_exclusive_u32_into(h.flags, h.pos, W, h.n_live, h.scan_part, s));
-    hipLaunchKernelGGL(k_compact_live, wgrid, dim3(WALK_THREADS), 0, s, h.flags, h.pos, W, h.next,
-                       h.live);
-    hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(64), 0, s, h.counters);
+    TW_HIP(scan_exclusive_u32(flags, pos, W, n_live, g->ws, s));
+    hipLaunchKernelGGL(k_compact_live, wgrid, dim3(WALK_THREADS), 0, s, flags, pos, W, next, live);
+    hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(64), 0, s, counters);
     with_kinds(a.hop.kind, TW_UNIFORM, [&](auto hk, auto) {
         auto launch = [&](auto kernel) {
             static const int maxb = resident_bpc(kernel);  // per instantiation
@@ -1682,7 +1680,7 @@ tw_status queue_hops_in(tw_graph* g, const WalkArgs& a, int bpc, const HopLists&
             const int64_t blocks =
                 std::min<int64_t>(ceil_div(W, WALK_THREADS), (int64_t)g->cu_count * b);
             hipLaunchKernelGGL(kernel, dim3((unsigned)std::max<int64_t>(blocks, 1)),
-                               dim3(WALK_THREADS), 0, s, a, h.live, h.prev, h.n_live, h.counters);
+                               dim3(WALK_THREADS), 0, s, a, live, prev, n_live, counters);
         };
         if (rows)
             launch(k_walk_hops<decltype(hk)::value, true>);
@@ -1692,29 +1690,6 @@ tw_status queue_hops_in(tw_graph* g, const WalkArgs& a, int bpc, const HopLists&
     TW_HIP(hipGetLastError());
     return TW_OK;
 }
-
-// The same with the lists in the graph's buffers (grown as needed).
-tw_status queue_hops(tw_graph* g, const WalkArgs& a, int bpc, Error& err) {
-    const int64_t W = a.num_walks;
-    DevBuf* bufs32[] = {&g->c_node0, &g->c_walk0, &g->c_node2, &g->c_walk2, &g->c_flags,
-                        &g->c_pos, &g->c_prev};
-    for (DevBuf* b : bufs32) TW_HIP(ensure(*b, sizeof(uint32_t) * W, g->stream));
-    TW_HIP(ensure(g->c_t0, sizeof(uint64_t) * W, g->stream));
-    TW_HIP(ensure(g->c_t2, sizeof(uint64_t) * W, g->stream));
-    TW_HIP(ensure(g->wq, sizeof(unsigned long long) * QUEUE_SLICES, g->stream));
-    TW_HIP(ensure(g->ws.scan_part, sizeof(uint32_t) * scan_parts_u32(W), g->stream));
-    HopLists h;
-    h.live = Live{g->c_node0.as<uint32_t>(), g->c_walk0.as<uint32_t>(), g->c_t0.as<uint64_t>()};
-    h.next = Live{g->c_node2.as<uint32_t>(), g->c_walk2.as<uint32_t>(), g->c_t2.as<uint64_t>()};
-    h.prev = g->c_prev.as<int32_t>();
-    h.flags = g->c_flags.as<uint32_t>();
-    h.pos = g->c_pos.as<uint32_t>();
-    h.n_live = g->scal.as<uint32_t>() + SLOT_U32_N_LIVE;
-    h.scan_part = g->ws.scan_part.as<uint32_t>();
-    h.counters = g->wq.as<unsigned long long>();
-    return queue_hops_in(g, a, bpc, h, err);
-}
-
 
 // Rounds of a block (64 walks each): more rounds keep more lanes busy, as
 // long as the launch still fills the chip (16 wavefronts a compute unit): a
@@ -1897,86 +1872,19 @@ tw_status sample_walks_batch(tw_graph* g, const tw_batch_params* p, int32_t* nod
     return queue_walks(vg, a, q, g->auto_bpc, err, rev);
 }
 
-// ---------------------------------------------------------------------------
-// Allocation-free walks: the queue dispatch of plain walks (queue_hops_in)
-// with its per-call lists in one file-scope device array, for callers that
-// cannot allocate device memory.
-
-namespace {
-
-constexpr int64_t NA_MAX = TW_NOALLOC_MAX_WALKS;
-constexpr int64_t na_round(int64_t b) { return (b + 255) / 256 * 256; }
-// byte offsets of the lists of NA_MAX walks inside the array
-constexpr int64_t NA_NODE0 = 0;
-constexpr int64_t NA_WALK0 = NA_NODE0 + na_round(4 * NA_MAX);
-constexpr int64_t NA_T0 = NA_WALK0 + na_round(4 * NA_MAX);
-constexpr int64_t NA_NODE2 = NA_T0 + na_round(8 * NA_MAX);
-constexpr int64_t NA_WALK2 = NA_NODE2 + na_round(4 * NA_MAX);
-constexpr int64_t NA_T2 = NA_WALK2 + na_round(4 * NA_MAX);
-constexpr int64_t NA_PREV = NA_T2 + na_round(8 * NA_MAX);
-constexpr int64_t NA_FLAGS = NA_PREV + na_round(4 * NA_MAX);
-constexpr int64_t NA_POS = NA_FLAGS + na_round(4 * NA_MAX);
-constexpr int64_t NA_NLIVE = NA_POS + na_round(4 * NA_MAX);
-constexpr int64_t NA_COUNTERS = NA_NLIVE + 256;
-constexpr int64_t NA_PART = NA_COUNTERS + na_round(8 * QUEUE_SLICES);
-// the scan's partial sums: one word per 256 walks bounds scan_parts_u32
-// (tiles of at least 256 elements, plus one); checked at set-up
-constexpr int64_t NA_PART_WORDS = NA_MAX / 256 + 2;
-constexpr int64_t NA_BYTES = NA_PART + na_round(4 * NA_PART_WORDS);
-
-// The lists of every allocation-free call on a device. Host code never
-// passes this name to a kernel: it stands for the device array only in
-// device code and in hipGetSymbolAddress, whose result (per device) is
-// what the kernels receive.
-static __device__ __align__(256) unsigned char scratch[NA_BYTES];
-
-constexpr int NA_DEVICES = 64;
-std::mutex na_mu;
-void* na_ptr[NA_DEVICES] = {};
-
-template <typename T>
-T* na_at(void* base, int64_t off) {
-    return reinterpret_cast<T*>(static_cast<unsigned char*>(base) + off);
-}
-
-}  // namespace
-
-// Once per device, with that device current: the device address of the
-// array (each device holds its own copy).
-tw_status noalloc_setup(int device, Error& err) {
-    if (device < 0 || device >= NA_DEVICES) {
-        err = Error{TW_EDEVICE, "allocation-free walks: device ordinal out of range"};
-        return err.code;
-    }
-    if (scan_parts_u32(NA_MAX) > NA_PART_WORDS) {
-        err = Error{TW_EDEVICE, "allocation-free walks: scan partials exceed their space"};
-        return err.code;
-    }
-    std::lock_guard<std::mutex> lk(na_mu);
-    if (na_ptr[device]) return TW_OK;
-    void* p = nullptr;
-    const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-    if (e != hipSuccess || !p) {
-        (void)hipGetLastError();
-        err = Error{TW_EDEVICE, std::string("allocation-free walks: hipGetSymbolAddress failed: ") +
-                                    hipGetErrorString(e)};
-        return err.code;
-    }
-    na_ptr[device] = p;
-    return TW_OK;
-}
-
-int64_t noalloc_scratch_bytes() { return NA_BYTES; }
-
+// Allocation-free walks, for callers that cannot allocate device memory: one
+// launch of the full-walk kernel, which keeps a walk's state in registers and
+// LDS. (The queue dispatch, with its lists in a device array, took five more
+// launches around it: 1,000 linear walks 85 -> 50 us.)
 tw_status sample_walks_noalloc(tw_graph* g, const tw_walk_params* p, int32_t* nodes, int64_t* ts,
                                int32_t* len, Error& err) {
     if (!p) {
         err = Error{TW_EINVAL, "sample_walks_noalloc: null params"};
         return err.code;
     }
-    if (p->num_walks > NA_MAX) {
+    if (p->num_walks > (int64_t)TW_NOALLOC_MAX_WALKS) {
         err = Error{TW_EINVAL, "sample_walks_noalloc: num_walks exceeds TW_NOALLOC_MAX_WALKS (" +
-                                   std::to_string(NA_MAX) + ")"};
+                                   std::to_string(TW_NOALLOC_MAX_WALKS) + ")"};
         return err.code;
     }
     if (p->direction != TW_FORWARD) {
@@ -1999,33 +1907,10 @@ tw_status sample_walks_noalloc(tw_graph* g, const tw_walk_params* p, int32_t* no
                     "built (one tw_sample_walks call with a node2vec bias builds it)"};
         return err.code;
     }
-    void* base = nullptr;
-    if (g->device >= 0 && g->device < NA_DEVICES) {
-        std::lock_guard<std::mutex> lk(na_mu);
-        base = na_ptr[g->device];
-    }
-    if (!base) {
-        err = Error{TW_EDEVICE, "sample_walks_noalloc: no device array for the graph's device"};
-        return err.code;
-    }
     WalkArgs a;
     if (prepare_plain(g, p, nodes, ts, len, a, err) != TW_OK) return err.code;
     if (p->num_walks == 0) return TW_OK;
-    HopLists h;
-    h.live = Live{na_at<uint32_t>(base, NA_NODE0), na_at<uint32_t>(base, NA_WALK0),
-                  na_at<uint64_t>(base, NA_T0)};
-    h.next = Live{na_at<uint32_t>(base, NA_NODE2), na_at<uint32_t>(base, NA_WALK2),
-                  na_at<uint64_t>(base, NA_T2)};
-    h.prev = na_at<int32_t>(base, NA_PREV);
-    h.flags = na_at<uint32_t>(base, NA_FLAGS);
-    h.pos = na_at<uint32_t>(base, NA_POS);
-    h.n_live = na_at<uint32_t>(base, NA_NLIVE);
-    h.scan_part = na_at<uint32_t>(base, NA_PART);
-    h.counters = na_at<unsigned long long>(base, NA_COUNTERS);
-    // the rows are padded first unless the kernels write them whole, as in
-    // tw_sample_walks
-    if (!own_rows(a)) launch_fill(g, a.nodes, a.ts, a.num_walks * (int64_t)a.L);
-    return queue_hops_in(g, a, g->auto_bpc, h, err);
+    return full_walks(g, a, false, err);
 }
 
 tw_status check_walk_params(const tw_walk_params* p, Error& err) {
