@@ -21,6 +21,12 @@ SOURCES = ["prim.hip", "index.hip", "nodeview.hip", "weights.hip", "adjacency.hi
 PROBE_LIB = os.path.join(HERE, "libtw_probe.so")
 PROBE_SOURCES = ["probe.hip"]
 
+# walk.hip: keep the FP64 functions' constants out of registers. Hoisted out of
+# the hop loops, the polynomial coefficients of log, exp and their variants held
+# up to 60 VGPRs for the whole walk: exponential hops took 128 VGPRs (66 now),
+# node2vec's 128 with 24 spilled (75), so fewer wavefronts were in flight.
+EXTRA_FLAGS = {"walk.hip": ["-mllvm", "-disable-machine-licm"]}
+
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950",
@@ -39,7 +45,7 @@ FLAGS = [
 
 def _compile(src: str, verbose: bool) -> str:
     obj = os.path.join(BUILD, src.replace(".hip", ".o"))
-    cmd = [HIPCC, *FLAGS, "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [HIPCC, *FLAGS, *EXTRA_FLAGS.get(src, []), "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -82,9 +82,8 @@ constexpr int WALK_THREADS = 256;
 
 // Kernels are instantiated per hop kind HK and start kind SK (-1: read at
 // run time). A fixed kind leaves only that picker's arithmetic in the
-// kernel: the full-walk kernel takes 52-56 VGPRs for uniform and linear hops
-// (8 wavefronts per SIMD) and about 100 for exponential hops, against 129
-// for the kernel that carries every picker (3 wavefronts per SIMD).
+// kernel: the full-walk kernel takes 58 VGPRs for uniform and linear hops and
+// 66 for exponential ones, against 92 for the kernel that carries every picker.
 template <int HK>
 __device__ __forceinline__ HopBias fixed_hop(HopBias h) {
     if (HK >= 0) h.kind = HK;
@@ -341,21 +340,27 @@ struct RowRing {
 
 // ------------------------------------------------------------- walk blocks
 //
-// A wavefront runs a block of up to 64 x rounds walks, a lane one walk at a
-// time: it takes every start of the block first (all lanes busy), keeps the
-// start states in LDS, and then hops; a lane whose walk has ended takes the
-// block's next start from LDS. Walks of one launch end after very different
-// numbers of hops (7 of 80 slots on average, 20 and more for the longest of
-// 64): with one walk per lane 34 % of the lanes of an instruction did work,
-// 18 % for node2vec, whose rejected trials also held the other lanes back, and
-// each lane padded its own row. The launches are bound by the random lines
-// they read and write (4M exponential walks of length 80 on 100M edges: 5.6
-// TB/s, the copy reaches 4.7), small ones by the chain of dependent loads.
-// One walk per lane -> blocks: that launch 3.75 -> 3.01 ms; 1M uniform walks of
-// 25 slots on an undirected graph 817 -> 731 us (rows of any width no longer
-// pre-filled); 2M node2vec walks 3.71 -> 2.65 ms; 1M weight-based 1.01 -> 0.88
-// ms; 1M backward exponential 1.02 -> 0.69 ms; 10,000 walks 22.1 -> 20.3 us
-// (workgroups of one wavefront; of four: 25.7).
+// A wavefront runs a block of 64 walks, a lane each, and writes their rows
+// whole: slots leave in chunks of eight through LDS, and when every walk of
+// the block has ended the wavefront pads all its rows together. A rejected
+// node2vec trial is an attempt of its own, so a lane whose trial was accepted
+// goes on to its next hop while others try again.
+//
+// Large launches are bound by the random lines they read and the lines they
+// write (4M exponential walks of length 80 on 100M edges: 5.6 TB/s of them, a
+// copy reaches 4.7), small ones by the chain of dependent loads; what helps is
+// wavefronts in flight (66 VGPRs for exponential hops, 75 for node2vec, 6.4 KB
+// of LDS: 5 to 6 a SIMD) and whole sectors in the writes. Against one walk per
+// lane that padded its own row in chunks of four, with FP64 constants hoisted
+// into 128 VGPRs (4 a SIMD): that launch 3.75 -> 2.96 ms; 1M uniform walks of 25
+// slots on an undirected graph 817 -> 605 us (rows of any width are no longer
+// pre-filled); 2M node2vec walks 3.71 -> 2.24 ms; 1M weight-based 1.01 -> 0.83
+// ms; 1M backward exponential 1.02 -> 0.68 ms; 10,000 walks 22.1 -> 18.2 us.
+// Also tried: blocks of 128 or 256 walks whose idle lanes take the next start
+// from LDS (busy lanes 48 % instead of 34 % of an instruction's, but fewer
+// wavefronts in flight: equal, node2vec 4 % faster, mixed batches 15 %
+// slower); chunks of 4 (5 % slower) and 16 (10-40 % slower); workgroups of
+// four wavefronts (10,000 walks 25.7 us against 20.3).
 
 // The walks of a block (uniform over the wavefront): walk j of the block is
 // walk w0 + j stride of its request, with RNG id id0 + j stride.
@@ -369,45 +374,31 @@ struct WalkBlock {
     int32_t* nodes;
     int64_t* ts;
     int32_t* len;
-    bool vec;              // nodes and ts 16-byte aligned: whole chunks leave as vectors
     uint32_t* range_flag;  // a start node out of range
     uint32_t* cap_count;   // walks node2vec's trial cap ended
-};
+    // ragged blocks: per-walk length limits (null: L) and row starts (null:
+    // rows of L slots) inside out_slots slots; a walk whose limit or row is
+    // out of range sets *bad_flag and writes nothing
+    const int32_t* limits;
+    const int64_t* rows;
+    int64_t out_slots;
+    uint32_t* bad_flag;
+    bool pad;  // the block pads its rows (else the outputs were pre-filled)
 
-// LDS of one wavefront: each lane's ring of its walk's current chunk of CH
-// output slots (its own column), and per walk of the block its start state and
-// its length.
-template <int CH>
-struct BlockLds {
-    int32_t* ring_n;
-    int64_t* ring_t;
-    int64_t* t;
-    int32_t *cur, *prev, *len;
-    __device__ BlockLds(unsigned char* base, int rounds) {
-        const int n = 64 * rounds;
-        ring_t = reinterpret_cast<int64_t*>(base);
-        t = ring_t + CH * 64;
-        ring_n = reinterpret_cast<int32_t*>(t + n);
-        cur = ring_n + CH * 64;
-        prev = cur + n;
-        len = prev + n;
+    // nodes and ts 16-byte aligned: four slots leave as vectors
+    __device__ __forceinline__ bool vec() const {
+        return (((uintptr_t)nodes | (uintptr_t)ts) & 15) == 0;
     }
 };
-constexpr int block_lds_bytes(int chunk, int rounds) {
-    return chunk * 64 * 12 + 64 * rounds * 20;
-}
-// Chunk and most rounds of a kind's blocks: what LDS holds for 16 wavefronts a
-// compute unit (10 KB each). Chunks of eight slots write whole sectors;
-// node2vec's long and uneven hops gain more from rounds (2M walks of length 40
-// on 50M edges: 2.65 ms with chunks of 4 and 4 rounds, 2.92 with 8 and 2;
-// 4M exponential walks of length 80 on 100M edges 3.19 against 3.05).
-constexpr int block_chunk(int kind) { return kind == TW_NODE2VEC || kind < 0 ? 4 : 8; }
-constexpr int block_max_rounds(int kind) { return kind == TW_NODE2VEC || kind < 0 ? 4 : 2; }
-static_assert(block_lds_bytes(8, 2) <= 10240 && block_lds_bytes(4, 4) <= 10240, "16 a CU");
 
-// idle lanes that make a wavefront end their rows and take new starts while
-// others still hop (1 and 16 measured alike, 32 slower on 1M-walk launches)
-constexpr int BLOCK_REFILL_MIN = 16;
+// LDS of a block: each lane's ring of its walk's current chunk (its own
+// column), and the rows' first slots left to pad.
+constexpr int CHUNK = 8;
+struct BlockLds {
+    int64_t ring_t[CHUNK][64];
+    int32_t ring_n[CHUNK][64];
+    int32_t at[64];
+};
 
 // LDS written by one lane of a wavefront and read by another: in program
 // order for the hardware, so only the compiler has to keep it
@@ -417,39 +408,36 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// A lane's output row. The row's slots are grouped in aligned chunks of CH (ph:
-// the row's first slot inside its first chunk), which leave for memory once
-// their last slot is known, as 16-byte stores where four slots belong to the
-// row (chunks of eight: 32 bytes of nodes and a whole 64-byte sector of
-// timestamps at once).
-template <int CH>
+// A lane's output row, from slot row0 of the outputs. Its slots are grouped
+// in aligned chunks (ph: the row's first slot inside its first chunk), which
+// leave for memory once their last slot is known, as 16-byte stores where four
+// slots belong to the row: 32 bytes of nodes and a whole 64-byte sector of
+// timestamps at once.
 struct RowOut {
     const WalkBlock& b;
-    const BlockLds<CH>& m;
+    BlockLds& m;
     int lane;
-    int j = -1;  // the walk of the block
-    int ph = 0;
-    __device__ __forceinline__ int64_t first() const { return (b.w0 + j * b.stride) * b.L; }
-    __device__ __forceinline__ void open(int jj) {
-        j = jj;
-        ph = (int)(first() & (CH - 1));
-    }
-    // The row's slots [from, to) of the chunk at slot q (a multiple of CH); the
-    // slots from `known` on are padding.
+    int64_t row0;
+    int32_t width;
+    int ph;
+    __device__ RowOut(const WalkBlock& b_, BlockLds& m_, int lane_, int64_t row, int32_t w)
+        : b(b_), m(m_), lane(lane_), row0(row), width(w), ph((int)(row & (CHUNK - 1))) {}
+    // The row's slots [from, to) of the chunk at slot q (a multiple of CHUNK);
+    // the slots from `known` on are padding.
     __device__ __forceinline__ void store(int64_t q, int from, int to, int known) const {
-        const int64_t at = first() - ph + q;
+        const int64_t at = row0 - ph + q;
 #pragma unroll
-        for (int k0 = 0; k0 < CH; k0 += 4) {
+        for (int k0 = 0; k0 < CHUNK; k0 += 4) {
             int32_t v[4];
             int64_t x[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                v[i] = k0 + i < known ? m.ring_n[(k0 + i) * 64 + lane] : -1;
-                x[i] = k0 + i < known ? m.ring_t[(k0 + i) * 64 + lane] : TS_NONE;
+                v[i] = k0 + i < known ? m.ring_n[k0 + i][lane] : -1;
+                x[i] = k0 + i < known ? m.ring_t[k0 + i][lane] : TS_NONE;
             }
             int32_t* n = b.nodes + at + k0;
             int64_t* t = b.ts + at + k0;
-            if (b.vec && from <= k0 && k0 + 4 <= to) {
+            if (b.vec() && from <= k0 && k0 + 4 <= to) {
                 *reinterpret_cast<int4*>(n) = make_int4(v[0], v[1], v[2], v[3]);
                 *reinterpret_cast<longlong2*>(t) = make_longlong2(x[0], x[1]);
                 *reinterpret_cast<longlong2*>(t + 2) = make_longlong2(x[2], x[3]);
@@ -465,25 +453,21 @@ struct RowOut {
     }
     __device__ __forceinline__ void push(int32_t p, int32_t v, int64_t t) const {
         const int64_t q = (int64_t)ph + p;
-        const int r = (int)(q & (CH - 1));
-        m.ring_n[r * 64 + lane] = v;
-        m.ring_t[r * 64 + lane] = t;
-        if (r == CH - 1) store(q - r, q - r < ph ? ph : 0, CH, CH);
+        const int r = (int)(q & (CHUNK - 1));
+        m.ring_n[r][lane] = v;
+        m.ring_t[r][lane] = t;
+        if (r == CHUNK - 1) store(q - r, q - r < ph ? ph : 0, CHUNK, CHUNK);
     }
-    // ends a row of len slots: the chunk of the last slot is completed with
-    // padding up to the row's end (the padding passes write the rest)
-    __device__ __forceinline__ void finish(int32_t len) const {
+    // Ends a row of len slots: the chunk of the last slot is completed with
+    // padding up to the row's end. Returns the first slot left to the padding
+    // passes.
+    __device__ __forceinline__ int32_t finish(int32_t len) const {
         const int64_t q = (int64_t)ph + len;
-        const int r = (int)(q & (CH - 1));
-        if (len == 0 || r == 0) return;
-        const int64_t c = q - r, end = (int64_t)ph + b.L - c;
-        store(c, c < ph ? ph : 0, end < CH ? (int)end : CH, r);
-    }
-    // first slot of a row that finish(len) leaves to the padding passes
-    __device__ static __forceinline__ int32_t written(int64_t row0, int32_t len, int32_t width) {
-        if (len == 0) return 0;
-        const int64_t ph = row0 & (CH - 1);
-        const int64_t at = ((ph + len + CH - 1) & ~(int64_t)(CH - 1)) - ph;
+        const int r = (int)(q & (CHUNK - 1));
+        if (len == 0 || r == 0) return len;
+        const int64_t c = q - r, end = (int64_t)ph + width - c;
+        store(c, c < ph ? ph : 0, end < CHUNK ? (int)end : CHUNK, r);
+        const int64_t at = c + CHUNK - ph;
         return at < width ? (int32_t)at : width;
     }
 };
@@ -605,145 +589,121 @@ __device__ __forceinline__ bool candidates(const WalkArgs& a, const NodeRec& r, 
 // it does not need is in flight)
 __device__ __forceinline__ void computed_here(uint64_t& x) { asm volatile("" : "+v"(x)); }
 
-// The walks of block b, by one wavefront. Each round of the loop is one
-// attempt of a hop per lane: node2vec's rejected trials are attempts of their
-// own, so a lane whose trial was accepted goes on to its next hop while
-// others try again.
-template <int HK, int SK, bool REV, int CH>
-__device__ __forceinline__ void walk_block(const WalkArgs& a, const WalkBlock& b,
-                                           const BlockLds<CH>& m) {
+// The walks of block b, by one wavefront (b.n <= 64). RAGGED: per-walk limits
+// and rows.
+template <int HK, int SK, bool REV, bool RAGGED>
+__device__ __forceinline__ void walk_block(const WalkArgs& a, const WalkBlock& b, BlockLds& m) {
     const int lane = threadIdx.x & 63;
     const HopBias hb = fixed_hop<HK>(b.hop);
     const StartParams sp = fixed_start<SK>(b.sp);
     const bool n2v = hb.kind == TW_NODE2VEC;
-#pragma unroll 1
-    for (int j = lane; j < b.n; j += 64) {
-        const int64_t w = b.w0 + j * b.stride;
-        const StartState st = walk_start(a, sp, w, b.id0 + (uint64_t)(j * b.stride), b.L, nullptr,
-                                         nullptr, REV, b.range_flag);
-        m.prev[j] = st.first;
-        m.cur[j] = st.cur;
-        m.t[j] = st.t;
-        m.len[j] = st.len;
+    const int64_t w = b.w0 + lane * b.stride;
+    const uint64_t id = b.id0 + (uint64_t)(lane * b.stride);
+    const bool mine = lane < b.n;
+    int32_t limit = b.L, width = b.L;
+    int64_t row0 = w * (int64_t)b.L;
+    if (RAGGED && mine) {
+        if (b.limits) limit = b.limits[w];
+        if (b.rows) {
+            row0 = b.rows[w];
+            width = limit;
+        }
+        if (limit < 1 || limit > b.L || row0 < 0 || row0 + limit > b.out_slots) {
+            atomicOr(b.bad_flag, 1u);
+            limit = 0;
+        }
     }
-    wave_lds_fence();
-
-    RowOut<CH> row{b, m, lane};
-    const int32_t& j = row.j;  // this lane's walk of the block (-1: none)
-    bool active = false;       // the walk goes on
-    int next = 0;
+    StartState st{0, 0, 0, 0, -1};
+    if (mine && limit > 0) st = walk_start(a, sp, w, id, limit, nullptr, nullptr, REV, b.range_flag);
+    const RowOut row(b, m, lane, row0, width);
+    int32_t len = st.len, cur = st.cur, prev = st.prev;
+    int64_t t = st.t;
+    if (len >= 1) row.push(0, st.first, TS_NONE);
+    if (len >= 2) row.push(1, cur, t);
+    bool active = len >= 2 && len < limit;
     uint32_t trial = 0;
-    int32_t len = 0, cur = 0, prev = 0;
-    int64_t t = 0;
     Candidates c{};
     ExpLaw law{};
-    while (true) {
-        // Lanes whose walk has ended keep its last chunk in LDS until enough
-        // of them wait (or no walk goes on): ending rows and taking starts
-        // costs the whole wavefront the same for one lane as for many.
-        const uint64_t busy = __ballot(active);
-        if (busy == 0 || (next < b.n && __popcll(busy) <= 64 - BLOCK_REFILL_MIN)) {
-            if (!active) {
-                if (j >= 0) {
-                    row.finish(len);
-                    m.len[j] = len;
-                }
-                const int at = next + __popcll(~busy & ((1ull << lane) - 1));
-                if (at < b.n) {
-                    row.open(at);
-                    prev = m.prev[at];
-                    cur = m.cur[at];
-                    t = m.t[at];
-                    len = m.len[at];
-                    trial = 0;
-                    if (len >= 1) row.push(0, prev, TS_NONE);
-                    if (len >= 2) row.push(1, cur, t);
-                    active = len >= 2 && len < b.L;
-                } else {
-                    row.j = -1;
-                }
-            }
-            if (busy == 0 && next >= b.n) break;  // every row has ended
-            next += 64 - __popcll(busy);
-        }
-        if (active) {
-            const bool fresh = !n2v || trial == 0;
-            NodeRec r;
-            if (fresh) r = a.rec[cur];
-            // hop len - 1 of the walk
-            Draw d = philox(b.id0 + (uint64_t)(j * b.stride), (uint64_t)(len - 1), trial, sp.seed);
+    while (active) {
+        const bool fresh = !n2v || trial == 0;
+        NodeRec r;
+        if (fresh) r = a.rec[cur];
+        // hop len - 1 of the walk; drawn while the record is on its way, except
+        // for node2vec, which needs the registers
+        Draw d;
+        if (!n2v) {
+            d = philox(id, (uint64_t)(len - 1), 0, sp.seed);
             computed_here(d.x0);
-            bool live = true;
-            if (fresh) {
-                live = candidates<REV>(a, r, t, reads_first_ts(hb.kind), c);
-                if (n2v && live)
-                    law = exp_law(c.c1 - c.c0, exp_lambda(c.t_lo, c.t_hi, c.c1 - c.c0, hb.tau));
-            }
-            if (!live) {
-                active = false;
-            } else {
-                Pick p;
-                bool take = true;
-                if (!REV && hb.kind == TW_WEIGHT) {
-                    p = pick_weight(a.ng, a.n_dst, a.cw, c.gb, c.c0, c.c1, c.end,
-                                    hb.tau > 0.0 ? hb.tau : 1.0, group_ts(a.ng, a.fence, r, c.c0),
-                                    c.t_hi, d);
-                } else if (n2v) {
-                    const uint32_t i = exp_draw(law, d.x0);
-                    p = edge_of_group(a.ng, a.n_dst, c.c1, c.end, REV ? c.c1 - 1 - i : c.c0 + i, d,
-                                      REV);
-                    // the edge prev -> candidate (backward: candidate -> prev
-                    // of the graph, which is prev -> candidate of the in-view)
-                    take = n2v_accept(a, hb, d.x2, prev, p.dst);
-                } else {
-                    p = pick_node(a.ng, a.n_dst, a.n_ts, c.c0, c.c1, c.end, hb.kind, hb.tau, c.t_lo,
-                                  c.t_hi, d, REV);
-                }
-                if (take) {
-                    row.push(len, p.dst, p.t);
-                    ++len;
-                    trial = 0;
-                    prev = cur;
-                    cur = p.dst;
-                    t = p.t;
-                    active = len < b.L;
-                } else if (++trial == N2V_MAX_TRIALS) {
-                    atomicAdd(b.cap_count, 1u);
-                    active = false;
-                }
-            }
+        }
+        bool live = true;
+        if (fresh) {
+            live = candidates<REV>(a, r, t, reads_first_ts(hb.kind), c);
+            if (n2v && live)
+                law = exp_law(c.c1 - c.c0, exp_lambda(c.t_lo, c.t_hi, c.c1 - c.c0, hb.tau));
+        }
+        if (n2v) d = philox(id, (uint64_t)(len - 1), trial, sp.seed);
+        if (!live) {
+            active = false;
+            continue;
+        }
+        Pick p;
+        bool take = true;
+        if (!REV && hb.kind == TW_WEIGHT) {
+            p = pick_weight(a.ng, a.n_dst, a.cw, c.gb, c.c0, c.c1, c.end,
+                            hb.tau > 0.0 ? hb.tau : 1.0, group_ts(a.ng, a.fence, r, c.c0), c.t_hi,
+                            d);
+        } else if (n2v) {
+            const uint32_t i = exp_draw(law, d.x0);
+            p = edge_of_group(a.ng, a.n_dst, c.c1, c.end, REV ? c.c1 - 1 - i : c.c0 + i, d, REV);
+            // the edge prev -> candidate (backward: candidate -> prev of the
+            // graph, which is prev -> candidate of the in-view)
+            take = n2v_accept(a, hb, d.x2, prev, p.dst);
+        } else {
+            p = pick_node(a.ng, a.n_dst, a.n_ts, c.c0, c.c1, c.end, hb.kind, hb.tau, c.t_lo,
+                          c.t_hi, d, REV);
+        }
+        if (take) {
+            row.push(len, p.dst, p.t);
+            ++len;
+            trial = 0;
+            prev = cur;
+            cur = p.dst;
+            t = p.t;
+            active = len < limit;
+        } else if (++trial == N2V_MAX_TRIALS) {
+            atomicAdd(b.cap_count, 1u);
+            active = false;
         }
     }
-    wave_lds_fence();
-    // lengths out; from here m.len holds each row's first slot left to pad
-    for (int k = lane; k < b.n; k += 64) {
-        const int64_t w = b.w0 + k * b.stride;
-        const int32_t l = m.len[k];
-        b.len[w] = l;
-        m.len[k] = RowOut<CH>::written(w * (int64_t)b.L, l, b.L);
+    if (mine) {
+        b.len[w] = len;
+        const int32_t at = row.finish(len);
+        m.at[lane] = at;
     }
+    if (!b.pad) return;
     wave_lds_fence();
-    if (b.vec && b.stride == 1 && b.L >= PAD_FLAT_MIN_L && b.L < PAD_FLAT_MAX_L) {
-        pad_rows_flat(b.nodes, b.ts, b.w0 * (int64_t)b.L, b.n, b.L, m.len, lane);
+    if (!RAGGED && b.vec() && b.L >= PAD_FLAT_MIN_L && b.L < PAD_FLAT_MAX_L) {
+        pad_rows_flat(b.nodes, b.ts, b.w0 * (int64_t)b.L, b.n, b.L, m.at, lane);
         return;
     }
     // 16 lanes a row
-    const int sub = lane & 15;
-    for (int k = lane >> 4; k < b.n; k += 4)
-        pad_row(b.nodes, b.ts, (b.w0 + k * b.stride) * (int64_t)b.L, m.len[k], b.L, b.vec, sub, 16);
+    for (int k = lane >> 4; k < b.n; k += 4) {
+        const int64_t wk = b.w0 + k * b.stride;
+        const int64_t rk = RAGGED && b.rows ? b.rows[wk] : wk * (int64_t)b.L;
+        const int32_t wid = RAGGED && b.rows && b.limits ? b.limits[wk] : b.L;
+        pad_row(b.nodes, b.ts, rk, m.at[k], wid, b.vec(), lane & 15, 16);
+    }
 }
 
 // The full-walk dispatch (Sec. "The Full-Walk Baseline"), forward and (REV, on
-// the in-view) backward: contiguous blocks of 64 x rounds walks, a workgroup of
-// one wavefront each, held to 4 wavefronts a SIMD (what the blocks' LDS allows).
+// the in-view) backward: contiguous blocks, a workgroup of one wavefront each.
 template <int HK, int SK, bool REV>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4)))
-k_walk_full(const WalkArgs a, int rounds) {
-    extern __shared__ __align__(16) unsigned char lds[];
-    const int per = 64 * rounds;
+k_walk_full(const WalkArgs a) {
+    __shared__ BlockLds lds;
     WalkBlock b;
-    b.w0 = (int64_t)blockIdx.x * per;
-    b.n = (int)std::min<int64_t>(per, a.num_walks - b.w0);
+    b.w0 = (int64_t)blockIdx.x * 64;
+    b.n = (int)std::min<int64_t>(64, a.num_walks - b.w0);
     b.stride = 1;
     b.id0 = a.base + (uint64_t)b.w0;
     b.L = a.L;
@@ -752,12 +712,10 @@ k_walk_full(const WalkArgs a, int rounds) {
     b.nodes = a.nodes;
     b.ts = a.ts;
     b.len = a.len;
-    b.vec = (((uintptr_t)a.nodes | (uintptr_t)a.ts) & 15) == 0;
     b.range_flag = &a.err[0];
     b.cap_count = &a.err[2];
-    constexpr int CH = block_chunk(HK);
-    walk_block<HK, SK, REV, CH>(a, b,
-                                BlockLds<CH>(lds, rounds));
+    b.pad = true;
+    walk_block<HK, SK, REV, false>(a, b, lds);
 }
 
 // Backward walks (Gamma-_t(v): in-edges of v with t' < t, the backward case
@@ -937,6 +895,73 @@ k_walk_queue(const WalkArgs a, const QueueArgs q) {
             }
         }
     }
+}
+
+// Whether the rows of a batch lie one after the other over all of its slots:
+// sets *gaps when some row does not end where the next begins (or a limit is
+// out of range).
+__global__ void k_rows_tile(const int64_t* __restrict__ row, const int32_t* __restrict__ max_len,
+                            int32_t L, int64_t n, int64_t out_slots, unsigned long long* gaps) {
+    bool bad = false;
+    for (int64_t i = (int64_t)blockIdx.x * WALK_THREADS + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * WALK_THREADS) {
+        const int32_t lim = max_len ? max_len[i] : L;
+        const int64_t end = i + 1 < n ? row[i + 1] : out_slots;
+        bad |= lim < 1 || lim > L || row[i] + lim != end || (i == 0 && row[0] != 0);
+    }
+    if (__ballot(bad) != 0 && (threadIdx.x & 63) == 0) atomicOr(gaps, 1ull);
+}
+
+// k_fill_outputs when *gaps is set
+__global__ void k_fill_gaps(int32_t* __restrict__ nodes, int64_t* __restrict__ ts, int64_t n,
+                            const unsigned long long* __restrict__ gaps) {
+    if (*gaps == 0) return;
+    fill_span(nodes, ts, 0, n, (int64_t)blockIdx.x * blockDim.x + threadIdx.x,
+              (int64_t)gridDim.x * blockDim.x);
+}
+
+// A batch in walk blocks. With several biases assigned by walk id (id mod
+// n_bias), a block takes the walks of one bias of a stretch of n_bias x 64
+// walks, so its wavefront runs one picker: lanes of six different biases ran
+// all six pickers one after the other. only >= 0: the launch runs the biases'
+// `only`-th walks of every stretch, with that bias's kernel (8M walks of
+// lengths 5-120 and six biases on a 40M-record graph: 12.7 ms with per-lane
+// biases on a work queue and a fill pass before it, 10.0 with one launch of
+// this kernel at 128 VGPRs, 7.4 with one launch a bias); else the blocks of a
+// stretch go to one XCD (every eighth workgroup), where the lines that
+// their rows share meet in its L2. The blocks pad their rows unless
+// pre_filled, or (gaps given) *gaps is set.
+template <int HK, int SK, bool REV>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4)))
+k_walk_batch(const WalkArgs a, const QueueArgs q, bool pre_filled,
+             const unsigned long long* __restrict__ gaps, int only) {
+    __shared__ BlockLds lds;
+    const int nb = q.n_bias;
+    WalkBlock b;
+    b.stride = nb;
+    if (only >= 0) {
+        b.w0 = (int64_t)blockIdx.x * nb * 64 + only;
+    } else {
+        const uint32_t xcd = blockIdx.x % NUM_XCD, i = blockIdx.x / NUM_XCD;
+        b.w0 = ((int64_t)(i / nb) * NUM_XCD + xcd) * nb * 64 + i % nb;
+    }
+    if (b.w0 >= a.num_walks) return;
+    b.n = (int)std::min<int64_t>(64, (a.num_walks - b.w0 + nb - 1) / nb);
+    b.id0 = a.base + (uint64_t)b.w0;
+    b.L = a.L;
+    b.sp = start_of(a);
+    b.hop = q.bias[b.id0 % (uint64_t)nb];
+    b.nodes = a.nodes;
+    b.ts = a.ts;
+    b.len = a.len;
+    b.range_flag = &a.err[0];
+    b.cap_count = &a.err[2];
+    b.limits = q.max_len;
+    b.rows = q.row;
+    b.out_slots = q.out_slots;
+    b.bad_flag = &a.err[3];
+    b.pad = gaps ? *gaps == 0 : !pre_filled;
+    walk_block<HK, SK, REV, true>(a, b, lds);
 }
 
 // Live walks between steps: current node, walk index, current timestamp.
@@ -1691,28 +1716,76 @@ tw_status queue_hops(tw_graph* g, const WalkArgs& a, int bpc, Error& err) {
     return TW_OK;
 }
 
-// Rounds of a block (64 walks each): more rounds keep more lanes busy, as
-// long as the launch still fills the chip (16 wavefronts a compute unit): a
-// 1M-walk launch is 8,192 blocks of 2 rounds for 4,096 places (weight-based
-// walks 0.88 ms, with 3 rounds 0.99).
-int block_rounds(const tw_graph* g, int64_t walks, int kind) {
-    const int64_t chip = (int64_t)g->cu_count * 16 * 64;
-    return (int)std::clamp<int64_t>(walks / chip, 1, block_max_rounds(kind));
-}
+// slots from which a batch with given rows checks whether they cover all of
+// them instead of filling them first
+constexpr int64_t BATCH_CHECK_SLOTS = 4 << 20;
 
 // the full-walk kernel; it writes whole rows, padding included
 tw_status full_walks(tw_graph* g, const WalkArgs& a, bool rev, Error& err) {
-    if (queue_shape(g, err) != TW_OK) return err.code;
-    const int rounds = block_rounds(g, a.num_walks, a.hop.kind);
-    const dim3 grid((unsigned)ceil_div(a.num_walks, (int64_t)64 * rounds));
-    const size_t lds = (size_t)block_lds_bytes(block_chunk(a.hop.kind), rounds);
+    const dim3 grid((unsigned)ceil_div(a.num_walks, 64));
     with_kinds(a.hop.kind, a.start_kind, [&](auto h, auto st) {
         with_direction(rev, decltype(h)::value, [&](auto r) {
             hipLaunchKernelGGL((k_walk_full<decltype(h)::value, decltype(st)::value,
                                             decltype(r)::value>),
-                               grid, dim3(64), lds, g->stream, a, rounds);
+                               grid, dim3(64), 0, g->stream, a);
         });
     });
+    TW_HIP(hipGetLastError());
+    return TW_OK;
+}
+
+// A batch whose biases go by walk id, in walk blocks.
+tw_status batch_blocks(tw_graph* g, const WalkArgs& a, const QueueArgs& q, Error& err, bool rev) {
+    if (queue_shape(g, err) != TW_OK) return err.code;
+    hipStream_t s = g->stream;
+    const int64_t W = a.num_walks, slots = q.out_slots;
+    // The blocks pad their own rows where the rows cover every slot: rows of L
+    // slots known here, given ones checked on the device. Small outputs are
+    // filled at once: the check and the conditional fill are two more launches
+    // (about 8 us, the time to fill 4M slots).
+    const unsigned long long* gaps = nullptr;
+    bool pre_filled = false;
+    if (!q.row && slots >= W * (int64_t)a.L) {
+        const int64_t used = W * (int64_t)a.L;
+        if (slots > used) launch_fill(g, a.nodes + used, a.ts + used, slots - used);
+    } else if (q.row && slots >= BATCH_CHECK_SLOTS) {
+        TW_HIP(ensure(g->wq, sizeof(unsigned long long) * QUEUE_SLICES, s));
+        unsigned long long* flag = g->wq.as<unsigned long long>();
+        hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(64), 0, s, flag);
+        hipLaunchKernelGGL(k_rows_tile,
+                           dim3((unsigned)std::min<int64_t>(ceil_div(W, WALK_THREADS), 2048)),
+                           dim3(WALK_THREADS), 0, s, q.row, q.max_len, a.L, W, slots, flag);
+        hipLaunchKernelGGL(k_fill_gaps, dim3(8192), dim3(WALK_THREADS), 0, s, a.nodes, a.ts, slots,
+                           flag);
+        gaps = flag;
+    } else {
+        launch_fill(g, a.nodes, a.ts, slots);
+        pre_filled = true;
+    }
+    const int nb = q.n_bias;
+    const int64_t stretches = ceil_div(W, (int64_t)64 * nb);
+    auto launch = [&](int hk, int only) {
+        const dim3 grid((unsigned)(only >= 0 ? stretches
+                                             : ceil_div(stretches, NUM_XCD) * NUM_XCD * nb));
+        with_kinds(hk, a.start_kind, [&](auto h, auto st) {
+            with_direction(rev, decltype(h)::value, [&](auto r) {
+                hipLaunchKernelGGL((k_walk_batch<decltype(h)::value, decltype(st)::value,
+                                                 decltype(r)::value>),
+                                   grid, dim3(64), 0, s, a, q, pre_filled, gaps, only);
+            });
+        });
+    };
+    // Several biases: one launch a bias, with the kernel that carries that
+    // picker only, where each fills the chip; else one launch of the kernel
+    // that carries all of them.
+    if (nb == 1) {
+        launch(q.bias[0].kind, -1);
+    } else if (W / nb < (int64_t)g->cu_count * 16 * 64) {
+        launch(-1, -1);
+    } else {
+        for (int o = 0; o < nb; ++o)
+            launch(q.bias[(a.base + (uint64_t)o) % (uint64_t)nb].kind, o);
+    }
     TW_HIP(hipGetLastError());
     return TW_OK;
 }
@@ -1867,6 +1940,12 @@ tw_status sample_walks_batch(tw_graph* g, const tw_batch_params* p, int32_t* nod
     }
     const int64_t slots = p->out_slots > 0 ? p->out_slots : p->num_walks * (int64_t)p->max_len;
     q.out_slots = slots;
+    // biases by walk id: walk blocks, a wavefront's walks all of one bias; given
+    // per walk: the work queue
+    // (ids that wrap past 2^64 would change the order of the biases: the queue)
+    if (p->dispatch != TW_DISPATCH_FULL_WALK && !p->d_bias &&
+        p->walk_id_base <= UINT64_MAX - (uint64_t)p->num_walks)
+        return batch_blocks(vg, a, q, err, rev);
     launch_fill(vg, nodes, ts, slots);
     if (p->dispatch == TW_DISPATCH_FULL_WALK) return batch_full_walk(vg, a, q, err, rev);
     return queue_walks(vg, a, q, g->auto_bpc, err, rev);

@@ -306,9 +306,16 @@ __device__ __forceinline__ Pick pick_node(const GroupRec* __restrict__ ng,
                                           bool rev = false) {
     if (kind == TW_UNIFORM) {
         const uint32_t c = ng[gc].first;
-        const uint32_t i = (uint32_t)scale_u64(d.x0, end - c);
-        const uint32_t e = rev ? end - 1 - i : c + i;
-        return Pick{n_dst[e], n_ts[e]};
+        const uint32_t n = end - c;
+        const uint32_t i = (uint32_t)scale_u64(d.x0, n);
+        const uint32_t k = rev ? n - 1 - i : i;
+        if (n == ge - gc) {
+            // one edge a group: the group's record holds the edge (one random
+            // line instead of two: 1M walks on an undirected graph 731 -> 611 us)
+            const GroupRec g = ng[gc + k];
+            return Pick{g.dst & 0x7fffffff, g.ts};
+        }
+        return Pick{n_dst[c + k], n_ts[c + k]};
     }
     const uint32_t n = ge - gc;
     const uint32_t i = pick_group(n, kind, tau, n > 1 ? t_first : 0, t_last, d.x0);

@@ -1,8 +1,9 @@
-"""Rows written by the full-walk kernel's blocks: every row width around its
-chunks of four and eight slots, launches of one partial block to several
-rounds a wavefront, outputs that are not 16-byte aligned, walks that never
-start. Against the queue dispatch, whose walks the oracle checks elsewhere;
-equal bit for bit."""
+"""Rows written by walk blocks: every row width around their chunks of eight
+slots, launches of one partial block to many, outputs that are not 16-byte
+aligned, walks that never start; batches whose blocks take one bias each,
+with given rows that do and do not cover the outputs. Against the queue
+dispatch and the one-thread-per-walk batch, whose walks the oracle checks
+elsewhere; equal bit for bit."""
 import numpy as np
 import pytest
 
@@ -53,12 +54,12 @@ def test_rows_of_any_width(L, shift, kind):
 
 @pytest.mark.parametrize("kind", ["uniform", "linear", "exponential", "node2vec", "weight"])
 @pytest.mark.parametrize("direction", ["forward", "backward"])
-def test_several_rounds_a_wavefront(kind, direction):
+def test_many_blocks(kind, direction):
     torch, tw = gpu_or_skip()
     if direction == "backward" and kind == "weight":
         pytest.skip("the weight-based picker walks forward only")
     g = _graph(torch, tw, directed=direction == "forward")
-    for W, L in ((1_100_003, 9), (700_001, 8)):
+    for W, L in ((300_003, 9), (70_001, 8)):
         kw = dict(hop_bias=kind, hop_tau=300.0, p=2.0, q=0.5, start_bias="linear", seed=L,
                   direction=direction)
         ref = g.sample_walks(W, L, dispatch="queue", **kw)
@@ -84,4 +85,52 @@ def test_bad_start_nodes_leave_padded_rows():
     with pytest.raises(tw.TwError) as e:
         g.sync()
     assert e.value.code == tw.TW_ERANGE
+    g.close()
+
+
+@pytest.mark.parametrize("direction", ["forward", "backward"])
+@pytest.mark.parametrize("W,L,base", [(1, 9, 0), (383, 12, 3), (385, 7, 2 ** 64 - 200),
+                                      (100_003, 60, 5), (1_600_001, 9, 1)])
+def test_batch_blocks(W, L, base, direction):
+    """Six biases by walk id, uneven limits: rectangular rows, packed rows
+    (above and below the size from which the rows are checked instead of
+    pre-filled) and rows with gaps, which keep their padding."""
+    torch, tw = gpu_or_skip()
+    g = _graph(torch, tw, directed=direction == "forward")
+    rng = np.random.default_rng(W)
+    lim = torch.from_numpy(rng.integers(1, L + 1, W).astype(np.int32)).cuda()
+    biases = [("uniform", 0.0, 1.0, 1.0), ("linear", 0.0, 1.0, 1.0), ("exponential", 300.0, 1.0, 1.0),
+              ("node2vec", 300.0, 0.5, 2.0), ("node2vec", 300.0, 1.0, 1.0),
+              ("node2vec", 300.0, 2.0, 0.5)]
+    kw = dict(max_lens=lim, start_bias="linear", seed=3, walk_id_base=base, direction=direction)
+    row, total = g.row_offsets(lim)
+    gap = row + torch.arange(W + 1, device="cuda") // 2  # a free slot after every second row
+    for rows in (None, (row, total), (gap, int(gap[-1]) + 3)):
+        ragged = dict(ragged=True, rows=rows) if rows is not None else {}
+        ref = g.sample_walks_batch(W, L, biases, dispatch="full_walk", **ragged, **kw)
+        out = g.sample_walks_batch(W, L, biases, dispatch="queue", **ragged, **kw)
+        for a, b in zip(out[:3], ref[:3]):
+            assert torch.equal(a, b), (rows is None,)
+    g.close()
+
+
+def test_batch_bad_limits_and_rows():
+    torch, tw = gpu_or_skip()
+    g = _graph(torch, tw)
+    W, L = 200_000, 30
+    biases = [("uniform", 0.0, 1.0, 1.0), ("linear", 0.0, 1.0, 1.0)]
+    lim = torch.full((W,), 30, dtype=torch.int32, device="cuda")
+    row, total = g.row_offsets(lim)
+    for where, bad in (("limit", 0), ("limit", 31), ("row", -1), ("row", W * 30 - 5)):
+        l2, r2 = lim.clone(), row.clone()
+        (l2 if where == "limit" else r2)[77] = bad
+        for rows in (None, (r2, total)) if where == "limit" else ((r2, total),):
+            ragged = dict(ragged=True, rows=rows) if rows is not None else {}
+            nodes, ts, lens, _ = g.sample_walks_batch(W, L, biases, max_lens=l2, seed=1, **ragged)
+            torch.cuda.synchronize()
+            assert int(lens[77]) == 0 and int(lens[78]) >= 2
+            assert bool((nodes.reshape(-1)[77 * 30:78 * 30] == -1).all())
+            with pytest.raises(tw.TwError) as e:
+                g.sync()
+            assert e.value.code == tw.TW_EINVAL
     g.close()
