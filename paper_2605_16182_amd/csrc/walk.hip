@@ -590,9 +590,9 @@ __device__ __forceinline__ bool candidates(const WalkArgs& a, const NodeRec& r, 
 __device__ __forceinline__ void computed_here(uint64_t& x) { asm volatile("" : "+v"(x)); }
 
 // The walks of block b, by one wavefront (b.n <= 64). RAGGED: per-walk limits
-// and rows.
+// and rows. Returns the length of the lane's walk.
 template <int HK, int SK, bool REV, bool RAGGED>
-__device__ __forceinline__ void walk_block(const WalkArgs& a, const WalkBlock& b, BlockLds& m) {
+__device__ __forceinline__ int32_t walk_block(const WalkArgs& a, const WalkBlock& b, BlockLds& m) {
     const int lane = threadIdx.x & 63;
     const HopBias hb = fixed_hop<HK>(b.hop);
     const StartParams sp = fixed_start<SK>(b.sp);
@@ -680,11 +680,11 @@ __device__ __forceinline__ void walk_block(const WalkArgs& a, const WalkBlock& b
         const int32_t at = row.finish(len);
         m.at[lane] = at;
     }
-    if (!b.pad) return;
+    if (!b.pad) return len;
     wave_lds_fence();
     if (!RAGGED && b.vec() && b.L >= PAD_FLAT_MIN_L && b.L < PAD_FLAT_MAX_L) {
         pad_rows_flat(b.nodes, b.ts, b.w0 * (int64_t)b.L, b.n, b.L, m.at, lane);
-        return;
+        return len;
     }
     // 16 lanes a row
     for (int k = lane >> 4; k < b.n; k += 4) {
@@ -693,6 +693,7 @@ __device__ __forceinline__ void walk_block(const WalkArgs& a, const WalkBlock& b
         const int32_t wid = RAGGED && b.rows && b.limits ? b.limits[wk] : b.L;
         pad_row(b.nodes, b.ts, rk, m.at[k], wid, b.vec(), lane & 15, 16);
     }
+    return len;
 }
 
 // The full-walk dispatch (Sec. "The Full-Walk Baseline"), forward and (REV, on
@@ -1097,16 +1098,16 @@ k_walk_hops(const WalkArgs a, Live live, const int32_t* __restrict__ prev_of,
 // ----------------------------------------------------------------- serve
 //
 // A serving launch: the walks of several requests, each with its own seed,
-// id base, length limit, hop and start bias, start nodes and output rows,
-// through the same work queue. Walk w of the launch belongs to the request r
-// with walk0[r] <= w < walk0[r] + count[r] and is that request's walk
-// w - walk0[r], so a request's result does not depend on what else shares
-// the launch.
+// id base, length limit, hop and start bias, start nodes and output rows, in
+// walk blocks: a block's walks are all of one request (the last one of a
+// request may be partial), so its parameters are uniform over the wavefront, it
+// runs one picker, and it writes its rows whole. A request's result does not
+// depend on what else shares the launch.
 
 constexpr int SERVE_MAX_REQ = 1024;
 
 struct ServeReqDev {
-    int64_t walk0, count;
+    int64_t block0, count;  // first block of the launch, walks
     uint64_t seed, base;
     int32_t L, start_kind, start_mode, pad;
     double start_tau;
@@ -1118,127 +1119,39 @@ struct ServeReqDev {
     uint32_t* err;  // the request's own words: [0] start node out of range, [1] trial-cap hits
 };
 
-// every picker's registers (about 180 VGPRs): held to 3 waves per SIMD
-// (a burst of 2,000 mixed requests: 3.53 G hops/s, against 3.37 at the 2
-// waves 180 VGPRs allow and 3.34 at 4, which spills 47 registers)
-// REV: backward requests on the in-view (each hop as in k_walk_back).
+// REV: backward requests on the in-view. Before, lanes took walks of any
+// request from a work queue (per-lane parameters, about 180 VGPRs held to 3
+// waves a SIMD) into rows that one fill launch per request had padded: 16
+// requests of 100 to 10,000 mixed walks 397 + 36 us of fills -> 316 us.
 template <bool REV>
-__global__ void __launch_bounds__(WALK_THREADS) __attribute__((amdgpu_waves_per_eu(3)))
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4)))
 k_walk_serve(const WalkArgs a, const ServeReqDev* __restrict__ reqs, int nreq,
-             unsigned long long* counters, unsigned long long* hops_out) {
-    __shared__ int64_t w0[SERVE_MAX_REQ];
-    for (int r = threadIdx.x; r < nreq; r += WALK_THREADS) w0[r] = reqs[r].walk0;
-    __syncthreads();
-    const int lane = threadIdx.x & 63;
-    const int64_t W = a.num_walks;  // walks of the launch
-    const int64_t slice_len = (W + QUEUE_SLICES - 1) / QUEUE_SLICES;
-    int slice = (int)(blockIdx.x % QUEUE_SLICES);
-    int exhausted = 0;
-    int64_t w = -1, i = 0;
-    uint64_t id = 0, hop = 0, hops = 0;
-    int32_t len = 0, lim = 0, cur = 0, prev = 0;
-    int64_t tcur = 0;
-    int32_t* out_n = nullptr;
-    int64_t* out_t = nullptr;
-    int32_t* out_len = nullptr;
-    uint32_t* rerr = nullptr;
-    StartParams sp{};
-    uint64_t seed = 0;
-    HopBias hb{};
-    while (true) {
-        const uint64_t idle = __ballot(w < 0);
-        if (idle && exhausted < QUEUE_SLICES) {
-            const int n = __popcll(idle);
-            const int leader = __ffsll((unsigned long long)idle) - 1;
-            unsigned long long got = 0;
-            if (lane == leader) got = atomicAdd(&counters[slice], (unsigned long long)n);
-            got = __shfl(got, leader, 64);
-            const int64_t lo = (int64_t)slice * slice_len;
-            const int64_t hi = lo + slice_len < W ? lo + slice_len : W;
-            if (w < 0) {
-                const int rank = __popcll(idle & ((1ull << lane) - 1));
-                const int64_t cand = lo + (int64_t)got + rank;
-                if (cand < hi) {
-                    w = cand;
-                    int rl = 0, rh = nreq;  // last request with walk0 <= w
-                    while (rh - rl > 1) {
-                        const int mid = (rl + rh) >> 1;
-                        if (w0[mid] <= w) rl = mid; else rh = mid;
-                    }
-                    const ServeReqDev& R = reqs[rl];
-                    i = w - R.walk0;
-                    seed = R.seed;
-                    sp = StartParams{R.seed, R.start_kind, R.start_mode, R.start_tau,
-                                     R.start_nodes};
-                    hb = R.hop;
-                    lim = R.L;
-                    id = R.base + (uint64_t)i;
-                    out_n = R.nodes + i * (int64_t)R.L;
-                    out_t = R.ts + i * (int64_t)R.L;
-                    out_len = R.len + i;
-                    rerr = R.err;
-                    const StartState st = walk_start(a, sp, i, id, lim, out_n, out_t, REV, rerr);
-                    len = st.len;
-                    cur = st.cur;
-                    prev = st.prev;
-                    tcur = st.t;
-                    hop = 1;
-                    if (len < 2 || len >= lim) {
-                        *out_len = len;
-                        hops += len > 1 ? (uint64_t)(len - 1) : 0;
-                        w = -1;
-                    }
-                }
-            }
-            if (lo + (int64_t)got + n >= hi) {
-                slice = (slice + 1) % QUEUE_SLICES;
-                ++exhausted;
-            }
-        }
-        if (__ballot(w >= 0) == 0) {
-            if (exhausted >= QUEUE_SLICES) break;
-            continue;
-        }
-        if (w >= 0) {
-            bool done = true;
-            const NodeRec r = a.rec[cur];
-            // forward: Gamma_t(cur) is empty when t >= the last timestamp;
-            // backward: when cur has no in-edge or none before t
-            bool live = REV ? r.gb != r.ge : tcur < r.t_last;
-            uint32_t g = 0;
-            if (live) {
-                if (REV) {
-                    g = tcur - 1 >= r.t_last
-                            ? r.ge
-                            : fence_search(a.ng, a.fence, r, tcur - 1, nullptr, 0, 0);
-                    live = g != r.gb;
-                } else {
-                    g = fence_search(a.ng, a.fence, r, tcur, nullptr, 0, 0);
-                }
-            }
-            if (live) {
-                Pick p;
-                int32_t nx;
-                if (REV ? back_pick(a, hb, seed, r, g, id, hop, prev, p, nx, rerr + 1)
-                        : hop_pick(a, hb, seed, r, g, id, hop, prev, p, nx, rerr + 1)) {
-                    out_n[len] = nx;
-                    out_t[len] = p.t;
-                    ++len;
-                    ++hop;
-                    prev = cur;
-                    cur = nx;
-                    tcur = p.t;
-                    done = len >= lim;
-                }
-            }
-            if (done) {
-                *out_len = len;
-                hops += (uint64_t)(len - 1);
-                w = -1;
-            }
-        }
-    }
-    // hops of the launch: one atomic per wavefront
+             unsigned long long* hops_out) {
+    __shared__ BlockLds lds;
+    const int lane = threadIdx.x;
+    // the block's request: the last one that starts at or before it (requests
+    // without walks start where the next one does)
+    int k = -1;
+    for (int i = 0; i < nreq; i += 64)
+        k += __popcll(__ballot(i + lane < nreq && reqs[i + lane].block0 <= (int64_t)blockIdx.x));
+    const ServeReqDev& R = reqs[__builtin_amdgcn_readfirstlane(k)];
+    WalkBlock b;
+    b.w0 = ((int64_t)blockIdx.x - R.block0) * 64;
+    b.n = (int)std::min<int64_t>(64, R.count - b.w0);
+    b.stride = 1;
+    b.id0 = R.base + (uint64_t)b.w0;
+    b.L = R.L;
+    b.sp = StartParams{R.seed, R.start_kind, R.start_mode, R.start_tau, R.start_nodes};
+    b.hop = R.hop;
+    b.nodes = R.nodes;
+    b.ts = R.ts;
+    b.len = R.len;
+    b.range_flag = R.err;
+    b.cap_count = R.err + 1;
+    b.pad = true;
+    const int32_t len = walk_block<-1, -1, REV, false>(a, b, lds);
+    // hops of the launch: one atomic a block
+    int32_t hops = len > 1 ? len - 1 : 0;
     for (int off = 32; off > 0; off >>= 1) hops += __shfl_down(hops, off, 64);
     if (lane == 0 && hops) atomicAdd(hops_out, (unsigned long long)hops);
 }
@@ -2055,7 +1968,7 @@ tw_status serve_launch(tw_graph* g, const ServeReq* reqs, int n, void* d_table, 
     }
     bool n2v = false;
     double wtau = NAN;  // the weight-based requests' time scale: one per launch
-    int64_t total = 0;
+    int64_t total = 0, blocks = 0;
     ServeReqDev* tab = static_cast<ServeReqDev*>(h_table);
     for (int r = 0; r < n; ++r) {
         const ServeReq& q = reqs[r];
@@ -2070,7 +1983,8 @@ tw_status serve_launch(tw_graph* g, const ServeReq* reqs, int n, void* d_table, 
         }
         n2v |= q.hop.kind == TW_NODE2VEC;
         ServeReqDev d{};
-        d.walk0 = total;
+        d.block0 = blocks;
+        blocks += ceil_div(q.count, 64);
         d.count = q.count;
         d.seed = q.seed;
         d.base = q.base;
@@ -2092,25 +2006,16 @@ tw_status serve_launch(tw_graph* g, const ServeReq* reqs, int n, void* d_table, 
     if (fill_args(g, total, 1, none, TW_START_EDGE, nullptr, 0, 0, n2v, wtau, nullptr, nullptr,
                   nullptr, a, err) != TW_OK)
         return err.code;
-    if (queue_shape(g, err) != TW_OK) return err.code;
-    TW_HIP(ensure(g->wq, sizeof(unsigned long long) * QUEUE_SLICES, g->stream));
     TW_HIP(hipMemcpyAsync(d_table, h_table, sizeof(ServeReqDev) * n, hipMemcpyHostToDevice,
                           g->stream));
-    for (int r = 0; r < n; ++r)
-        if (reqs[r].count > 0)
-            launch_fill(g, reqs[r].nodes, reqs[r].ts, reqs[r].count * (int64_t)reqs[r].max_len);
-    hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(64), 0, g->stream,
-                       g->wq.as<unsigned long long>());
-    if (total > 0) {
-        const int64_t blocks = std::min<int64_t>(ceil_div(total, WALK_THREADS),
-                                                 (int64_t)g->cu_count * g->queue_bpc_max);
+    if (blocks > 0) {
         const ServeReqDev* tab_d = static_cast<const ServeReqDev*>(d_table);
         if (rev)
-            hipLaunchKernelGGL(k_walk_serve<true>, dim3((unsigned)blocks), dim3(WALK_THREADS), 0,
-                               g->stream, a, tab_d, n, g->wq.as<unsigned long long>(), d_hops);
+            hipLaunchKernelGGL(k_walk_serve<true>, dim3((unsigned)blocks), dim3(64), 0, g->stream,
+                               a, tab_d, n, d_hops);
         else
-            hipLaunchKernelGGL(k_walk_serve<false>, dim3((unsigned)blocks), dim3(WALK_THREADS), 0,
-                               g->stream, a, tab_d, n, g->wq.as<unsigned long long>(), d_hops);
+            hipLaunchKernelGGL(k_walk_serve<false>, dim3((unsigned)blocks), dim3(64), 0, g->stream,
+                               a, tab_d, n, d_hops);
     }
     TW_HIP(hipGetLastError());
     return TW_OK;
