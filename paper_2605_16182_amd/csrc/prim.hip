@@ -690,10 +690,14 @@ hipError_t group_starts(int has_last, int64_t last_ts, const int64_t* ts, int64_
     return compact(op, n, total, ws.tiles, ws, s);
 }
 
-hipError_t radix_sort_u64(uint64_t* keys, uint32_t* vals, int64_t n, int bit_lo, int bit_hi,
-                          Workspace& ws, hipStream_t s) {
-    return radix_sort_impl<uint64_t>(keys, vals, nullptr, keys, vals, nullptr, n, bit_lo, bit_hi,
-                                     ws, s);
+hipError_t radix_sort_pairs(uint32_t* keys, uint64_t* pay, int64_t n, int bits, Workspace& ws,
+                            hipStream_t s) {
+    return radix_sort_impl<uint32_t>(keys, nullptr, pay, keys, nullptr, pay, n, 0, bits, ws, s);
+}
+
+hipError_t radix_sort_pairs(uint64_t* keys, uint64_t* pay, int64_t n, int bits, Workspace& ws,
+                            hipStream_t s) {
+    return radix_sort_impl<uint64_t>(keys, nullptr, pay, keys, nullptr, pay, n, 0, bits, ws, s);
 }
 
 hipError_t radix_sort_u32(uint32_t* keys, uint32_t* vals, int64_t n, int bit_lo, int bit_hi,

@@ -256,10 +256,14 @@ hipError_t group_starts(int has_last, int64_t last_ts, const int64_t* ts, int64_
 // Stable LSD radix sort of (keys, vals) by bits [bit_lo, bit_hi) of the key.
 // vals may be null. Result ends in keys / vals. The alternate buffers come
 // from the workspace.
-hipError_t radix_sort_u64(uint64_t* keys, uint32_t* vals, int64_t n, int bit_lo, int bit_hi,
-                          Workspace& ws, hipStream_t s);
 hipError_t radix_sort_u32(uint32_t* keys, uint32_t* vals, int64_t n, int bit_lo, int bit_hi,
                           Workspace& ws, hipStream_t s);
+// Stable sort of 32- or 64-bit keys by their low `bits` bits, carrying a
+// 64-bit payload, in place.
+hipError_t radix_sort_pairs(uint32_t* keys, uint64_t* pay, int64_t n, int bits, Workspace& ws,
+                            hipStream_t s);
+hipError_t radix_sort_pairs(uint64_t* keys, uint64_t* pay, int64_t n, int bits, Workspace& ws,
+                            hipStream_t s);
 // Stable sort of (kin, vin, win) by bits [bit_lo, bit_hi) of kin into
 // (kout, vout, wout), carrying a 32-bit and a 64-bit payload (either may be
 // null). The inputs are only read; no pass writes into them unless they are
@@ -387,7 +391,7 @@ struct tw_graph {
     int auto_bpc = 0;
 
     // batch staging
-    tw::DevBuf b_src, b_dst, b_ts, b_keys, b_vals, b_flags;
+    tw::DevBuf b_src, b_dst, b_ts, b_keys, b_vals, b_flags, b_parts;
     tw::DevBuf flags, idx;             // per-edge temporaries
     tw::DevBuf v_flags, v_pos;         // per-node temporaries
     tw::DevBuf err;                    // device error flags (uint32)
@@ -404,7 +408,7 @@ struct tw_graph {
                 &o_flag, &o_rank, &o_tf, &f_tf, &adj_tab,
                 &c_node0, &c_walk0, &c_t0, &c_node1, &c_walk1, &c_t1, &c_node2, &c_walk2,
                 &c_t2, &c_prev, &c_flags, &c_pos, &wq,
-                &b_src, &b_dst, &b_ts, &b_keys, &b_vals, &b_flags, &flags, &idx, &v_flags,
+                &b_src, &b_dst, &b_ts, &b_keys, &b_vals, &b_flags, &b_parts, &flags, &idx, &v_flags,
                 &v_pos, &err, &scal, &ws.scan_part, &ws.hist, &ws.keys_alt, &ws.vals_alt,
                 &ws.v64_alt, &ws.tiles, &cw, &w_tiles};
     }
