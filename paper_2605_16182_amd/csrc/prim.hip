@@ -141,6 +141,54 @@ __global__ void k_scan_down(const In* in, V* out, int64_t n, const V* __restrict
 template <typename V>
 __global__ void k_set(V* p, V v) { *p = v; }
 
+// Scans of up to SCAN_ONE_MAX elements in one launch of one workgroup, a
+// thread its own consecutive elements: for these the two launches above are
+// launch time (about 6 us each in a small ingest, which makes nine scans).
+constexpr int SCAN_ONE_THREADS = 1024;
+constexpr int64_t SCAN_ONE_MAX = 16 * SCAN_ONE_THREADS;
+
+// exclusive scan of one value per thread over a 1024-thread block
+template <typename V>
+__device__ inline V block_excl_scan_1024(V v, V* total) {
+    __shared__ V wsum[SCAN_ONE_THREADS / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const V inc = wave_incl_scan(v);
+    if (lane == 63) wsum[wave] = inc;
+    __syncthreads();
+    V before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < SCAN_ONE_THREADS / 64; ++w) {
+        const V s = wsum[w];
+        before += (w < wave) ? s : 0;
+        all += s;
+    }
+    *total = all;
+    return before + inc - v;
+}
+
+template <typename In, typename V>
+__device__ __forceinline__ void scan_one(const In* in, V* out, int64_t n, V* total) {
+    const int per = (int)((n + SCAN_ONE_THREADS - 1) / SCAN_ONE_THREADS);
+    const int64_t b = (int64_t)threadIdx.x * per;
+    const int64_t e = b + per < n ? b + per : n;
+    V s = 0;
+    for (int64_t i = b; i < e; ++i) s += (V)in[i];
+    V all;
+    V run = block_excl_scan_1024(s, &all);
+    for (int64_t i = b; i < e; ++i) {  // in and out may alias: own elements only
+        const V x = (V)in[i];
+        out[i] = run;
+        run += x;
+    }
+    if (total && threadIdx.x == 0) *total = all;
+}
+
+template <typename In, typename V>
+__global__ void __launch_bounds__(SCAN_ONE_THREADS) k_scan_one(const In* in, V* out, int64_t n,
+                                                               V* total) {
+    scan_one<In, V>(in, out, n, total);
+}
+
 // Four u32 scans at once (array blockIdx.y of the launch): the same steps
 // as above, one launch each instead of one per array.
 struct Scan4 {
@@ -155,6 +203,12 @@ __device__ inline int64_t scan_count(int64_t n, const uint32_t* n_dev) {
     if (!n_dev) return n;
     const int64_t c = (int64_t)n_dev[0] + (int64_t)n_dev[1];
     return c < n ? c : n;
+}
+
+__global__ void __launch_bounds__(SCAN_ONE_THREADS) k_scan4_one(const Scan4 a, int64_t cap,
+                                                                const uint32_t* n_dev) {
+    const int y = blockIdx.x;
+    scan_one<uint32_t, uint32_t>(a.in[y], a.out[y], scan_count(cap, n_dev), a.total[y]);
 }
 
 __global__ void k_scan4_reduce(const Scan4 a, int64_t cap, uint32_t* __restrict__ part,
@@ -463,6 +517,98 @@ k_rs_scatter(const K* __restrict__ keys, const uint32_t* __restrict__ vals,
     }
 }
 
+// A sort of up to RS_ONE items in one launch of one workgroup of 16
+// wavefronts: the items stay in registers between passes (wavefront w holds
+// slots [256 w, 256 w + 256), 64 a round), each pass ranks them as the tiles
+// above do and exchanges them through LDS. A small sort is launches otherwise:
+// four a pass, two or three passes, two sorts an ingest (2,000 undirected
+// edges into a 400,000-record window, with the one-launch scans: 59 launches and
+// 397 us an ingest and its walks -> 39 and 327).
+// W64, PACK as in k_rs_scatter.
+constexpr int RS_ONE_THREADS = 1024;
+constexpr int RS_ONE_ITEMS = 4;
+constexpr int RS_ONE = RS_ONE_THREADS * RS_ONE_ITEMS;
+
+template <typename K, bool W64, bool PACK>
+__global__ void __launch_bounds__(RS_ONE_THREADS)
+k_rs_one(const K* keys, const uint32_t* vals, const uint64_t* v64, int n, int bit_lo, int bit_hi,
+         K* keys_out, uint32_t* vals_out, uint64_t* v64_out, uint64_t pack_base) {
+    constexpr int WAVES = RS_ONE_THREADS / 64, I = RS_ONE_ITEMS, RADIX = 256;
+    using Stage = std::conditional_t<W64 || sizeof(K) == 8, uint64_t, uint32_t>;
+    __shared__ uint32_t cnt[WAVES][RADIX];
+    __shared__ Stage stage[RS_ONE];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint64_t lower = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    K k[I];
+    uint32_t v[I];
+    uint64_t w[W64 ? I : 1];
+#pragma unroll
+    for (int r = 0; r < I; ++r) {
+        const int i = wave * 64 * I + r * 64 + lane;
+        k[r] = i < n ? keys[i] : K(0);
+        v[r] = (vals && i < n) ? vals[i] : 0u;
+        if constexpr (PACK) w[r] = i < n ? ((v64[i] - pack_base) << 32) | v[r] : 0ull;
+        else if constexpr (W64) w[r] = i < n ? v64[i] : 0ull;
+    }
+    const int passes = (bit_hi - bit_lo + 7) / 8, per = (bit_hi - bit_lo + passes - 1) / passes;
+    for (int p = 0; p < passes; ++p) {
+        const int shift = bit_lo + per * p;
+        const int nbits = bit_hi - shift < per ? bit_hi - shift : per;
+        const uint32_t mask = (1u << nbits) - 1u;
+        for (int d = tid; d < WAVES * RADIX; d += RS_ONE_THREADS) (&cnt[0][0])[d] = 0;
+        __syncthreads();
+        uint32_t at[I];
+#pragma unroll
+        for (int r = 0; r < I; ++r) {
+            const bool valid = wave * 64 * I + r * 64 + lane < n;
+            const uint32_t d = (uint32_t)(k[r] >> shift) & mask;
+            const uint64_t peers = digit_peers<8>(d, valid, nbits);
+            const uint32_t before = cnt[wave][d];
+            at[r] = before + (uint32_t)__popcll(peers & lower);
+            if (valid && (peers & lower) == 0) cnt[wave][d] = before + (uint32_t)__popcll(peers);
+        }
+        __syncthreads();
+        // starts of the digits, then of each wavefront's items in them
+        uint32_t pre[WAVES], tot = 0, all;
+        if (tid < RADIX)
+#pragma unroll
+            for (int x = 0; x < WAVES; ++x) {
+                pre[x] = tot;
+                tot += cnt[x][tid];
+            }
+        const uint32_t start = block_excl_scan_1024<uint32_t>(tot, &all);
+        if (tid < RADIX)
+#pragma unroll
+            for (int x = 0; x < WAVES; ++x) cnt[x][tid] = start + pre[x];
+        __syncthreads();
+        // the items' new places, one array at a time through the staging area
+        auto exchange = [&](auto* x) {
+            using X = std::remove_reference_t<decltype(x[0])>;
+            X* st = reinterpret_cast<X*>(stage);
+#pragma unroll
+            for (int r = 0; r < I; ++r)
+                if (wave * 64 * I + r * 64 + lane < n) st[at[r]] = x[r];
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < I; ++r) x[r] = st[wave * 64 * I + r * 64 + lane];
+            __syncthreads();
+        };
+#pragma unroll
+        for (int r = 0; r < I; ++r) at[r] += cnt[wave][(uint32_t)(k[r] >> shift) & mask];
+        exchange(k);
+        if (!PACK && vals) exchange(v);
+        if constexpr (W64) exchange(w);
+    }
+#pragma unroll
+    for (int r = 0; r < I; ++r) {
+        const int i = wave * 64 * I + r * 64 + lane;
+        if (i >= n) continue;
+        keys_out[i] = k[r];
+        if (!PACK && vals) vals_out[i] = v[r];
+        if constexpr (W64) v64_out[i] = w[r];
+    }
+}
+
 // keys copied and (val, v64) packed as in k_rs_scatter<.., PACK>, for sorts
 // with no pass to do it
 template <typename K>
@@ -503,6 +649,17 @@ hipError_t radix_sort_impl(const K* kin0, const uint32_t* vin0, const uint64_t* 
                 return e;
         }
         return hipSuccess;
+    }
+    if (n <= RS_ONE) {
+        auto one = [&](auto w64, auto packed) {
+            hipLaunchKernelGGL((k_rs_one<K, decltype(w64)::value, decltype(packed)::value>), dim3(1),
+                               dim3(RS_ONE_THREADS), 0, s, kin0, has_v || pack ? vin0 : nullptr,
+                               win0, (int)n, bit_lo, bit_hi, kout, vout, wout, pack_base);
+        };
+        if (pack) one(std::true_type{}, std::true_type{});
+        else if (has_w) one(std::true_type{}, std::false_type{});
+        else one(std::false_type{}, std::false_type{});
+        return hipGetLastError();
     }
     // 9-bit digits where they save a pass (26-bit node ids: 3 passes, not 4)
     const bool wide = ceil_div(bit_hi - bit_lo, 9) < ceil_div(bit_hi - bit_lo, 8);
@@ -613,6 +770,11 @@ hipError_t scan_core(const In* in, V* out, int64_t n, V* total, V* part, hipStre
         if (total) hipLaunchKernelGGL(k_set<V>, dim3(1), dim3(1), 0, s, total, (V)0);
         return hipGetLastError();
     }
+    if (n <= SCAN_ONE_MAX) {
+        hipLaunchKernelGGL((k_scan_one<In, V>), dim3(1), dim3(SCAN_ONE_THREADS), 0, s, in, out, n,
+                           total);
+        return hipGetLastError();
+    }
     const int64_t nb = ceil_div(n, SCAN_TILE);
     hipLaunchKernelGGL((k_scan_reduce<In, V>), dim3(nb), dim3(SCAN_THREADS), 0, s, in, n, part);
     if (nb <= SCAN_SUM_MAX_BLOCKS) {
@@ -629,7 +791,7 @@ hipError_t scan_core(const In* in, V* out, int64_t n, V* total, V* part, hipStre
 template <typename In, typename V>
 hipError_t scan_exclusive(const In* in, V* out, int64_t n, V* total, DevBuf& part_buf,
                           hipStream_t s) {
-    if (n > 0) {
+    if (n > SCAN_ONE_MAX) {
         const hipError_t e = ensure(part_buf, sizeof(V) * (ceil_div(n, SCAN_TILE) + 1), s);
         if (e != hipSuccess) return e;
     }
@@ -653,6 +815,10 @@ hipError_t scan_exclusive_u32x4(const uint32_t* const in[4], uint32_t* const out
     if (n <= 0) {
         for (int y = 0; y < 4; ++y)
             if (total[y]) hipLaunchKernelGGL(k_set<uint32_t>, dim3(1), dim3(1), 0, s, total[y], 0u);
+        return hipGetLastError();
+    }
+    if (n <= SCAN_ONE_MAX) {
+        hipLaunchKernelGGL(k_scan4_one, dim3(4), dim3(SCAN_ONE_THREADS), 0, s, a, n, n_dev);
         return hipGetLastError();
     }
     const int64_t nb = ceil_div(n, SCAN_TILE);
