@@ -397,14 +397,28 @@ __device__ __forceinline__ Elem job_elem(const Job& J, uint32_t i, const int32_t
     return bt.elem(J.bf + k);
 }
 
-// timestamp of element i of job J's written run
-__device__ __forceinline__ int64_t job_ts(const Job& J, uint32_t i, const int64_t* __restrict__ ots,
-                                          const BatchRuns& bt) {
-    if (J.kind == JOB_APPEND) return bt.t(J.bf + i);
+// Timestamps of elements i and i - 1 (i > 0) of job J's written run. In a
+// merge the element before output i is the later of the two runs' last
+// elements among the first i, so one search serves both.
+__device__ __forceinline__ void job_ts2(const Job& J, uint32_t i, const int64_t* __restrict__ ots,
+                                        const BatchRuns& bt, int64_t& x, int64_t& before) {
     const uint32_t na = J.oe - J.ob;
-    if (!J.merge) return i < na ? ots[J.ob + i] : bt.t(J.bf + i - na);
-    uint32_t k;
-    return merge_pick(J, i, ots, bt, &k) ? ots[J.ob + k] : bt.t(J.bf + k);
+    if (J.kind != JOB_APPEND && J.merge) {
+        uint32_t k;
+        const bool old = merge_pick(J, i, ots, bt, &k);
+        const uint32_t a = old ? k : i - k, b = i - a;  // of the first i outputs
+        x = old ? ots[J.ob + k] : bt.t(J.bf + k);
+        before = INT64_MIN;
+        if (a > 0) before = ots[J.ob + a - 1];
+        if (b > 0) before = std::max(before, bt.t(J.bf + b - 1));
+        return;
+    }
+    const auto at = [&](uint32_t e) {
+        if (J.kind == JOB_APPEND) return bt.t(J.bf + e);
+        return e < na ? ots[J.ob + e] : bt.t(J.bf + e - na);
+    };
+    x = at(i);
+    before = i > 0 ? at(i - 1) : INT64_MIN;
 }
 
 // last j in [lo, hi] with off[j] <= t (off[lo] <= t)
@@ -503,9 +517,10 @@ __global__ void __launch_bounds__(T) k_job_flags(const Job* __restrict__ jobs,
                 const Job J = jobs[j];
                 const uint32_t jb = M == 2 ? off[tj.j0] : tj.template start<S>(off, soff, j);
                 const uint32_t i = (uint32_t)(t - jb);
-                const int64_t x = job_ts(J, i, ots, bt);
+                int64_t x, before;
+                job_ts2(J, i, ots, bt, x, before);
                 if (i == 0) start = J.kind != JOB_APPEND || x != J.t_last;
-                else start = x != job_ts(J, i - 1, ots, bt);
+                else start = x != before;
             }
             const uint64_t b = __ballot(start);
             if (lane == 0 && t0 < total) bm[t0 >> 6] = b;
@@ -1108,7 +1123,10 @@ tw_status execute_jobs(tw_graph* g, int64_t nj, uint64_t out, const int32_t* sds
         TW_HIP(ensure(g->f_tf, sizeof(uint32_t) * (fcap / NV_TILE + 2), g->stream));
         hipLaunchKernelGGL(k_tile_first_dev, dim3(FENCE_GRID / 8), dim3(T), 0, s,
                            g->j_fw.as<uint32_t>(), nj, g->f_tf.as<uint32_t>());
-        hipLaunchKernelGGL(k_job_fence, dim3(FENCE_GRID), dim3(T), 0, s, jobs,
+        // at most FENCE_FAN words a level and job
+        const int64_t ft = ceil_div(nj * FENCE_MAX_LEVELS * FENCE_FAN, NV_TILE);
+        hipLaunchKernelGGL(k_job_fence, dim3((unsigned)std::min<int64_t>(ft, FENCE_GRID)), dim3(T), 0,
+                           s, jobs,
                            g->j_fw.as<uint32_t>(), g->f_tf.as<uint32_t>(), nj,
                            g->rec.as<NodeRec>(), dfence);
     }
