@@ -61,6 +61,9 @@ __device__ __forceinline__ NodeRec empty_rec() {
     r.gb = r.ge = r.g0 = r.ee = 0;
     r.fence_off = r.lv = 0;
     r.t_last = INT64_MIN;
+    r.t_prev = INT64_MIN;
+    r.last_first = 0;
+    r.last_dst = 0;
     r.kbase = r.pad = 0;
     return r;
 }
@@ -751,6 +754,7 @@ __global__ void k_job_finish(const Job* __restrict__ jobs, const uint32_t* __res
     if (J.kind == JOB_EVICT) {
         r.gb = J.ogb;
         if (r.gb >= r.ge) r = empty_rec();
+        else if (r.ge - r.gb == 1) r.t_prev = INT64_MIN;
     } else {
         const uint64_t cap = seg_groups(J.gcode);
         if (J.kind == JOB_APPEND) {
@@ -783,7 +787,11 @@ __global__ void k_job_finish(const Job* __restrict__ jobs, const uint32_t* __res
         r.fence_off = J.f0;
         r.lv = (uint32_t)fence_levels(r.ge - J.g0) | (J.gcode << 8) | (J.kshift << 16);
         r.kbase = J.kbase;
-        r.t_last = ngd[r.ge - 1].ts;
+        const GroupRec last = ngd[r.ge - 1];
+        r.t_last = last.ts;
+        r.last_first = last.first;
+        r.last_dst = last.dst;
+        r.t_prev = r.ge - r.gb > 1 ? ngd[r.ge - 2].ts : INT64_MIN;
     }
     rec[J.v] = r;
     fw[j] = f;

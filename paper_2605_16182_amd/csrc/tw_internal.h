@@ -27,26 +27,31 @@ struct alignas(16) GroupRec {
     int32_t dst;
 };
 
-// One record per node, 48 bytes, read at the start of every hop (three
-// independent 16-byte loads). A node's edges
-// and groups live in a segment of the edge and group pools: the live groups
-// are [gb, ge), the live edges end at ee (they start at the first edge of
-// group gb). g0 is the segment's first group (a multiple of FENCE_FAN), the
-// origin of the node's fence; fence_off is where the fence starts in the
-// fence pool; lv = levels in use | (capacity code << 8) | (key shift << 16),
-// the segment holding FENCE_FAN << code groups. t_last is the last live
-// timestamp (INT64_MIN for a node without edges), so a hop that cannot
-// continue stops after this load. kbase is the fence's key base (the
+// One record per node, 64 bytes (half a line, never two), read at the start of
+// every hop. A node's edges and groups live in a segment of the edge and group
+// pools: the live groups are [gb, ge), the live edges end at ee (they start at
+// the first edge of group gb). g0 is the segment's first group (a multiple of
+// FENCE_FAN), the origin of the node's fence; fence_off is where the fence
+// starts in the fence pool; lv = levels in use | (capacity code << 8) | (key
+// shift << 16), the segment holding FENCE_FAN << code groups. t_last is the
+// last live timestamp (INT64_MIN for a node without edges), so a hop that
+// cannot continue stops after this load. kbase is the fence's key base (the
 // segment's first group timestamp): with the shift here, a search needs no
-// load before its first fence window.
-struct alignas(16) NodeRec {
+// load before its first fence window. The last group's first edge and its
+// destination (as in its GroupRec) are kept here with t_prev, the timestamp of
+// the group before it (INT64_MIN: none): a hop from t_prev on has that one
+// group to pick from and reads nothing else.
+struct alignas(64) NodeRec {
     uint32_t gb, ge, g0, ee;
     uint32_t fence_off, lv;
     int64_t t_last;
     int64_t kbase;
+    int64_t t_prev;
+    uint32_t last_first;
+    int32_t last_dst;
     int64_t pad;
 };
-static_assert(sizeof(NodeRec) == 48, "three 16-byte loads");
+static_assert(sizeof(NodeRec) == 64, "half a line");
 __host__ __device__ inline uint32_t rec_levels(uint32_t lv) { return lv & 0xffu; }
 __host__ __device__ inline uint32_t rec_code(uint32_t lv) { return (lv >> 8) & 0xffu; }
 __host__ __device__ inline uint32_t rec_shift(uint32_t lv) { return (lv >> 16) & 0xffu; }

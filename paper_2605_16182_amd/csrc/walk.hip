@@ -557,18 +557,25 @@ struct Candidates {
 
 // Gamma_t of the node of record r: forward the groups after t, backward (on
 // the in-view) those before t; false when there is none. rate: the pick reads
-// the first candidate's timestamp.
+// the first candidate's timestamp. (node2vec, which reads the group's record in
+// every trial, searches as ever: the shortcut took its kernel from 79 to 81
+// VGPRs, five wavefronts a SIMD instead of six.)
 template <bool REV>
 __device__ __forceinline__ bool candidates(const WalkArgs& a, const NodeRec& r, int64_t t,
-                                           bool rate, Candidates& c) {
+                                           bool rate, bool n2v, Candidates& c) {
     c.gb = r.gb;
     if (!REV) {
         if (t >= r.t_last) return false;
-        c.c0 = fence_search(a.ng, a.fence, r, t, nullptr, 0, 0);
         c.c1 = r.ge;
         c.end = r.ee;
-        c.t_lo = rate ? group_ts(a.ng, a.fence, r, c.c0) : 0;
         c.t_hi = r.t_last;
+        if (!n2v && t >= r.t_prev) {  // the last group only
+            c.c0 = r.ge - 1;
+            c.t_lo = r.t_last;
+            return true;
+        }
+        c.c0 = fence_search(a.ng, a.fence, r, t, nullptr, 0, 0);
+        c.t_lo = rate ? group_ts(a.ng, a.fence, r, c.c0) : 0;
         return true;
     }
     if (r.gb == r.ge) return false;
@@ -583,6 +590,17 @@ __device__ __forceinline__ bool candidates(const WalkArgs& a, const NodeRec& r, 
     c.t_lo = rate ? group_ts(a.ng, a.fence, r, r.gb) : 0;
     c.t_hi = rate ? group_ts(a.ng, a.fence, r, hi - 1) : 0;
     return true;
+}
+
+// The pick when a node's last group is the one candidate (weight-based: a
+// one-edge group only, its edges are picked by weight): from the node record
+// alone, but for a group of several edges.
+__device__ __forceinline__ Pick pick_last(const int32_t* __restrict__ n_dst, const NodeRec& r,
+                                          int kind, const Draw& d) {
+    if (r.last_dst < 0) return Pick{r.last_dst & 0x7fffffff, r.t_last};
+    const uint32_t j =
+        (uint32_t)scale_u64(kind == TW_UNIFORM ? d.x0 : d.x1, r.ee - r.last_first);
+    return Pick{n_dst[r.last_first + j], r.t_last};
 }
 
 // keeps a value's computation above this point (a draw made while a load
@@ -637,7 +655,7 @@ __device__ __forceinline__ int32_t walk_block(const WalkArgs& a, const WalkBlock
         }
         bool live = true;
         if (fresh) {
-            live = candidates<REV>(a, r, t, reads_first_ts(hb.kind), c);
+            live = candidates<REV>(a, r, t, reads_first_ts(hb.kind), n2v, c);
             if (n2v && live)
                 law = exp_law(c.c1 - c.c0, exp_lambda(c.t_lo, c.t_hi, c.c1 - c.c0, hb.tau));
         }
@@ -648,7 +666,9 @@ __device__ __forceinline__ int32_t walk_block(const WalkArgs& a, const WalkBlock
         }
         Pick p;
         bool take = true;
-        if (!REV && hb.kind == TW_WEIGHT) {
+        if (!REV && !n2v && c.c0 + 1 == c.c1 && (hb.kind != TW_WEIGHT || r.last_dst < 0)) {
+            p = pick_last(a.n_dst, r, hb.kind, d);
+        } else if (!REV && hb.kind == TW_WEIGHT) {
             p = pick_weight(a.ng, a.n_dst, a.cw, c.gb, c.c0, c.c1, c.end,
                             hb.tau > 0.0 ? hb.tau : 1.0, group_ts(a.ng, a.fence, r, c.c0), c.t_hi,
                             d);

@@ -134,3 +134,32 @@ def test_batch_bad_limits_and_rows():
                 g.sync()
             assert e.value.code == tw.TW_EINVAL
     g.close()
+
+
+@pytest.mark.parametrize("directed", [True, False])
+@pytest.mark.parametrize("start_mode", ["edge", "node"])
+def test_hops_to_the_last_group(directed, start_mode):
+    """Nodes of few groups, of one edge and of several, under a window that
+    evicts down to one group and appends that join the last one: hops whose
+    only candidate is the node's last group are answered from its record."""
+    torch, tw = gpu_or_skip()
+    rng = np.random.default_rng(11)
+    V, W = 60, 20_000
+    g = tw.Graph(V, directed=directed, window=8)
+    t0 = 0
+    for b in range(12):
+        n = int(rng.integers(5, 120))
+        ts = t0 + np.sort(rng.integers(0, 4, n)).astype(np.int64)
+        t0 = int(ts[-1])  # the next batch may continue the last timestamp
+        g.ingest_batch(*to_dev(torch, rng.integers(0, V, n).astype(np.int32),
+                               rng.integers(0, V, n).astype(np.int32), ts))
+        if b == 6:
+            g.evict_before(t0)
+        starts = torch.from_numpy(rng.integers(0, V, W).astype(np.int32)).cuda()
+        for kind in ("uniform", "linear", "exponential", "node2vec", "weight"):
+            kw = dict(hop_bias=kind, hop_tau=2.0, p=0.5, q=2.0, seed=b, start_mode=start_mode,
+                      start_nodes=starts)
+            ref = g.sample_walks(W, 8, dispatch="queue", **kw)
+            for a, r in zip(g.sample_walks(W, 8, dispatch="full_walk", **kw), ref):
+                assert torch.equal(a, r), (b, kind)
+    g.close()
