@@ -121,7 +121,8 @@ def probe_rates(torch, dev):
     return best, copy_best
 
 
-WALK_SOURCES = ("paper_2605_16182_amd/csrc/walk.hip", "paper_2605_16182_amd/csrc/walk_device.h",
+WALK_SOURCES = ("paper_2605_16182_amd/csrc/walk.hip", "paper_2605_16182_amd/csrc/walk_kernels.h",
+                "paper_2605_16182_amd/csrc/walk_device.h",
                 "paper_2605_16182_amd/csrc/tw_internal.h")
 TRAFFIC_FILES = {"single": os.path.join(ROOT, "profiles", "walk_traffic_single_100M.txt"),
                  "stream": os.path.join(ROOT, "profiles", "walk_traffic_stream_1B.txt")}

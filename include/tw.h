@@ -145,8 +145,9 @@ typedef struct {
 } tw_walk_params;
 
 /*
- * A batch of walks of uneven lengths and mixed hop biases, run as one
- * persistent launch with a device work queue (TW_DISPATCH_QUEUE). Walk i has
+ * A batch of walks of uneven lengths and mixed hop biases: biases by walk id
+ * (d_bias NULL) run in blocks of walks of one bias, given ones in one
+ * persistent launch with a device work queue. Walk i has
  * RNG id walk_id_base + i, length limit d_max_len[i] (or max_len), hop bias
  * hop_biases[d_bias[i]] (or hop_biases[(walk_id_base + i) mod num_biases]),
  * and writes its nodes and timestamps at d_row[i] (or i * max_len). A walk's
@@ -170,8 +171,8 @@ typedef struct {
     int64_t out_slots;           /* slots of d_nodes and d_ts, padded by the call;
                                     0 with d_row NULL: num_walks * max_len */
     int32_t dispatch;            /* TW_DISPATCH_QUEUE (AUTO means it), or
-                                    TW_DISPATCH_FULL_WALK: one thread per walk, no
-                                    queue (the plain form, for comparison) */
+                                    TW_DISPATCH_FULL_WALK: one thread per walk in id
+                                    order, rows pre-filled (for comparison) */
     int32_t direction;           /* tw_direction (0: forward); backward walks take
                                     no TW_WEIGHT bias */
 } tw_batch_params;
@@ -302,10 +303,10 @@ tw_status tw_walk_layout(const tw_graph* g, uint64_t* out);
 tw_status tw_index_stats(const tw_graph* g, int64_t out[8]);
 
 /*
- * Walks of a tw_batch_params batch in one persistent launch (see there).
- * d_nodes: int32[out_slots], d_ts: int64[out_slots]; every slot is first set
- * to -1 / INT64_MIN, then each walk writes its nodes and timestamps from its
- * row start (position 0 of d_ts stays INT64_MIN). Rows must not overlap and
+ * Walks of a tw_batch_params batch (see there).
+ * d_nodes: int32[out_slots], d_ts: int64[out_slots]; each walk's nodes and
+ * timestamps from its row start (position 0 of d_ts is INT64_MIN), every other
+ * slot -1 / INT64_MIN. Rows must not overlap and
  * must fit in out_slots (the caller's layout; tw_row_offsets gives a packed
  * one). d_len: int32[num_walks] lengths. Stream-ordered, no synchronisation;
  * a limit outside [1, max_len], a bias index >= num_biases, or a row that
@@ -400,7 +401,7 @@ tw_status tw_sample_walks_noalloc(tw_graph* g, const tw_walk_params* params, int
  * the server exists), a worker thread and an ingest thread with a stream of
  * its own. Requests (tw_walk_params, dispatch ignored) and ingest batches
  * are queued in submission order. The worker packs consecutive requests
- * into one work-queue launch on the graph's stream (up to
+ * into one launch on the graph's stream (up to
  * max_walks_per_launch walks, 1024 requests) as soon as their outputs are
  * placed, without waiting for the launch before it (up to max_inflight
  * launches enqueued). A batch that reaches the front is planned (staged,

@@ -16,7 +16,7 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(ROOT, "_build", "tw")
 LIB = os.path.join(HERE, "libtw.so")
 SOURCES = ["prim.hip", "index.hip", "nodeview.hip", "weights.hip", "adjacency.hip", "walk.hip",
-           "serve.hip", "capi.hip"]
+           "queue.hip", "serve.hip", "capi.hip"]
 # roofline probes for the benchmark, a separate library
 PROBE_LIB = os.path.join(HERE, "libtw_probe.so")
 PROBE_SOURCES = ["probe.hip"]
@@ -24,7 +24,9 @@ PROBE_SOURCES = ["probe.hip"]
 # walk.hip: keep the FP64 functions' constants out of registers. Hoisted out of
 # the hop loops, the polynomial coefficients of log, exp and their variants held
 # up to 60 VGPRs for the whole walk: exponential hops took 128 VGPRs (66 now),
-# node2vec's 128 with 24 spilled (75), so fewer wavefronts were in flight.
+# node2vec's 128 with 24 spilled (75), so fewer wavefronts were in flight. (Not
+# for queue.hip, whose kernels write rows piecemeal and lose 10-15 % with more
+# wavefronts in flight.)
 EXTRA_FLAGS = {"walk.hip": ["-mllvm", "-disable-machine-licm"]}
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
