@@ -313,6 +313,8 @@ __device__ __forceinline__ int32_t walk_block(const WalkArgs& a, const WalkBlock
         if (limit < 1 || limit > b.L || row0 < 0 || row0 + limit > b.out_slots) {
             atomicOr(b.bad_flag, 1u);
             limit = 0;
+        } else if (row0 + width > b.out_slots) {
+            width = (int32_t)(b.out_slots - row0);  // the last row of outputs cut short
         }
     }
     StartState st{0, 0, 0, 0, -1};

@@ -163,3 +163,47 @@ def test_hops_to_the_last_group(directed, start_mode):
             for a, r in zip(g.sample_walks(W, 8, dispatch="full_walk", **kw), ref):
                 assert torch.equal(a, r), (b, kind)
     g.close()
+
+
+def test_rows_cut_short_by_the_outputs():
+    """Rectangular rows over fewer slots than walks x width (out_slots of the
+    C interface): walks whose limit still fits are written, the others are
+    refused, and nothing is written past the last slot."""
+    import ctypes
+
+    torch, tw = gpu_or_skip()
+    g = _graph(torch, tw)
+    W, L, short = 500, 13, 500 * 13 - 6
+    lim = torch.full((W,), 5, dtype=torch.int32, device="cuda")
+    lim[W - 1] = 7
+    lim[7] = 13
+    starts = torch.zeros(W, dtype=torch.int32, device="cuda")
+
+    def run(max_lens, slots):
+        nodes = torch.full((W * L + 16,), 7, dtype=torch.int32, device="cuda")
+        ts = torch.full((W * L + 16,), 7, dtype=torch.int64, device="cuda")
+        lens = torch.full((W,), 7, dtype=torch.int32, device="cuda")
+        biases = (tw._Bias * tw.MAX_BIASES)()
+        for i in range(2):
+            biases[i] = tw._Bias(i, 0.0, 1.0, 1.0)
+        prm = tw._BatchParams(W, L, tw._ptr(max_lens), 2, biases, None, tw._Bias(0, 0.0, 1.0, 1.0),
+                              tw.START_NODE, tw._ptr(starts), 3, 0, None, slots,
+                              tw.DISPATCH["queue"], 0)
+        tw._check(tw.lib().tw_sample_walks_batch(g._h, ctypes.byref(prm), tw._ptr(nodes),
+                                                 tw._ptr(ts), tw._ptr(lens)))
+        torch.cuda.synchronize()
+        return nodes, ts, lens
+
+    ref = run(lim, W * L)
+    nodes, ts, lens = run(lim, short)  # the last row has 7 slots: its limit just fits
+    g.sync()
+    assert torch.equal(nodes[:short], ref[0][:short]) and torch.equal(ts[:short], ref[1][:short])
+    assert torch.equal(lens, ref[2])
+    assert bool((nodes[short:] == 7).all()) and bool((ts[short:] == 7).all())
+    lim[W - 1] = 8
+    nodes, ts, lens = run(lim, short)
+    assert int(lens[W - 1]) == 0 and bool((nodes[short:] == 7).all())
+    with pytest.raises(tw.TwError) as e:
+        g.sync()
+    assert e.value.code == tw.TW_EINVAL
+    g.close()
