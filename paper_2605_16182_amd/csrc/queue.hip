@@ -131,7 +131,7 @@ __global__ void k_queue_reset(unsigned long long* counters) {
 
 // REFILL = false is the same per-walk work without the queue: thread i runs
 // walk i only (the full-walk form of a batch). REV: backward walks on the
-// in-view (each hop as in k_walk_back).
+// in-view.
 template <bool REFILL, int HK, int SK, bool REV = false>
 // The instantiation for mixed hop kinds (HK < 0) carries every picker's
 // registers (about 160 VGPRs, 3 waves per SIMD); it is held to 4 waves, which

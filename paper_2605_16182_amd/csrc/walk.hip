@@ -744,7 +744,7 @@ tw_status prepare_plain(tw_graph* g, const tw_walk_params* p, int32_t* nodes, in
 
 }  // namespace
 
-// Backward walks on the in-view: the full-walk kernel k_walk_back (AUTO,
+// Backward walks on the in-view: the full-walk kernel (AUTO,
 // FULL_WALK) or the work queue (QUEUE).
 tw_status sample_backward(tw_graph* g, const tw_walk_params* p, int32_t* nodes, int64_t* ts,
                           int32_t* len, Error& err) {
