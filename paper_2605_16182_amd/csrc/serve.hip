@@ -449,9 +449,12 @@ void worker_loop(tw_server* S) {
         }
         if (!progressed) {
             if (!S->inflight.empty()) {
-                // a launch is running: poll its event
+                // a launch is running: poll its event. A sleep ends about 50 us
+                // late (the kernel's timer slack), so a short one polls every 55
+                // us: with 50 us, every 105, a 500k-edge batch with 16 requests
+                // took 1.59 ms instead of 1.42
                 lk.unlock();
-                std::this_thread::sleep_for(std::chrono::microseconds(50));
+                std::this_thread::sleep_for(std::chrono::microseconds(5));
                 lk.lock();
             } else {
                 S->cv_work.wait_for(lk, std::chrono::milliseconds(5));
