@@ -176,7 +176,7 @@ k_walk_queue(const WalkArgs a, const QueueArgs q) {
                     const uint32_t b = q.bias_idx ? q.bias_idx[w] : (uint32_t)(id % (uint64_t)q.n_bias);
                     const int64_t row = q.row ? q.row[w] : w * (int64_t)a.L;
                     if (lim < 1 || lim > a.L || b >= (uint32_t)q.n_bias || row < 0 ||
-                        row + lim > q.out_slots) {
+                        row > q.out_slots - lim) {  // a sum could wrap
                         atomicOr(&a.err[3], 1u);
                         a.len[w] = 0;
                         w = -1;

@@ -310,7 +310,8 @@ __device__ __forceinline__ int32_t walk_block(const WalkArgs& a, const WalkBlock
             row0 = b.rows[w];
             width = limit;
         }
-        if (limit < 1 || limit > b.L || row0 < 0 || row0 + limit > b.out_slots) {
+        // (no sum: a row start near INT64_MAX would wrap past the check)
+        if (limit < 1 || limit > b.L || row0 < 0 || row0 > b.out_slots - limit) {
             atomicOr(b.bad_flag, 1u);
             limit = 0;
         } else if (row0 + width > b.out_slots) {
@@ -436,8 +437,9 @@ __global__ void k_rows_tile(const int64_t* __restrict__ row, const int32_t* __re
     for (int64_t i = (int64_t)blockIdx.x * WALK_THREADS + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * WALK_THREADS) {
         const int32_t lim = max_len ? max_len[i] : L;
-        const int64_t end = i + 1 < n ? row[i + 1] : out_slots;
-        bad |= lim < 1 || lim > L || row[i] + lim != end || (i == 0 && row[0] != 0);
+        const uint64_t end = (uint64_t)(i + 1 < n ? row[i + 1] : out_slots);
+        bad |= lim < 1 || lim > L || (uint64_t)row[i] + (uint64_t)lim != end ||
+               (i == 0 && row[0] != 0);
     }
     if (__ballot(bad) != 0 && (threadIdx.x & 63) == 0) atomicOr(gaps, 1ull);
 }
