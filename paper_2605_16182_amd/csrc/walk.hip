@@ -656,6 +656,9 @@ constexpr int64_t BATCH_CHECK_SLOTS = 4 << 20;
 tw_status batch_blocks(tw_graph* g, const WalkArgs& a, const QueueArgs& q, Error& err, bool rev) {
     if (queue_shape(g, err) != TW_OK) return err.code;
     hipStream_t s = g->stream;
+    // whichever batch comes first: a later one may be under graph capture,
+    // which must not allocate
+    TW_HIP(ensure(g->wq, sizeof(unsigned long long) * QUEUE_SLICES, s));
     const int64_t W = a.num_walks, slots = q.out_slots;
     // The blocks pad their own rows where the rows cover every slot: rows of L
     // slots known here, given ones checked on the device. Small outputs are
@@ -667,7 +670,6 @@ tw_status batch_blocks(tw_graph* g, const WalkArgs& a, const QueueArgs& q, Error
         const int64_t used = W * (int64_t)a.L;
         if (slots > used) launch_fill(g, a.nodes + used, a.ts + used, slots - used);
     } else if (q.row && slots >= BATCH_CHECK_SLOTS) {
-        TW_HIP(ensure(g->wq, sizeof(unsigned long long) * QUEUE_SLICES, s));
         unsigned long long* flag = g->wq.as<unsigned long long>();
         hipLaunchKernelGGL(k_clear_word, dim3(1), dim3(1), 0, s, flag);
         hipLaunchKernelGGL(k_rows_tile,
