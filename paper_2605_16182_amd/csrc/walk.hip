@@ -526,18 +526,19 @@ struct ServeReqDev {
 // requests of 100 to 10,000 mixed walks 397 + 36 us of fills -> 316 us.
 template <bool REV>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4)))
-k_walk_serve(const WalkArgs a, const ServeReqDev* __restrict__ reqs, int nreq,
+k_walk_serve(const WalkArgs a, const ServeReqDev* __restrict__ reqs, int nreq, int64_t block0,
              unsigned long long* hops_out) {
     __shared__ BlockLds lds;
     const int lane = threadIdx.x;
+    const int64_t block = block0 + blockIdx.x;
     // the block's request: the last one that starts at or before it (requests
     // without walks start where the next one does)
     int k = -1;
     for (int i = 0; i < nreq; i += 64)
-        k += __popcll(__ballot(i + lane < nreq && reqs[i + lane].block0 <= (int64_t)blockIdx.x));
+        k += __popcll(__ballot(i + lane < nreq && reqs[i + lane].block0 <= block));
     const ServeReqDev& R = reqs[__builtin_amdgcn_readfirstlane(k)];
     WalkBlock b;
-    b.w0 = ((int64_t)blockIdx.x - R.block0) * 64;
+    b.w0 = (block - R.block0) * 64;
     b.n = (int)std::min<int64_t>(64, R.count - b.w0);
     b.stride = 1;
     b.id0 = R.base + (uint64_t)b.w0;
@@ -633,6 +634,10 @@ void launch_fill(tw_graph* g, int32_t* nodes, int64_t* ts, int64_t slots) {
                            std::min<int64_t>(ceil_div(slots, 4 * WALK_THREADS), 8192), 1)),
                        dim3(WALK_THREADS), 0, g->stream, nodes, ts, slots);
 }
+
+// Most walks one launch of walk blocks takes: a launch holds fewer than 2^32
+// threads (a batch's grid is rounded up to eight stretches of 64 walks a bias).
+constexpr int64_t BLOCK_MAX_WALKS = (1ll << 32) - 8 * 64 * (TW_MAX_BIASES + 1);
 
 // the full-walk kernel; it writes whole rows, padding included
 tw_status full_walks(tw_graph* g, const WalkArgs& a, bool rev, Error& err) {
@@ -862,8 +867,9 @@ tw_status sample_walks_batch(tw_graph* g, const tw_batch_params* p, int32_t* nod
     q.out_slots = slots;
     // biases by walk id: walk blocks, a wavefront's walks all of one bias; given
     // per walk: the work queue
-    // (ids that wrap past 2^64 would change the order of the biases: the queue)
-    if (p->dispatch != TW_DISPATCH_FULL_WALK && !p->d_bias &&
+    // (the queue also where ids wrap past 2^64, which changes the order of the
+    // biases, and for more walks than a launch of blocks holds)
+    if (p->dispatch != TW_DISPATCH_FULL_WALK && !p->d_bias && p->num_walks <= BLOCK_MAX_WALKS &&
         p->walk_id_base <= UINT64_MAX - (uint64_t)p->num_walks)
         return batch_blocks(vg, a, q, err, rev);
     launch_fill(vg, nodes, ts, slots);
@@ -958,7 +964,8 @@ tw_status serve_launch(tw_graph* g, const ServeReq* reqs, int n, void* d_table, 
         err = Error{TW_EINVAL, "serve: 1..1024 requests per launch"};
         return err.code;
     }
-    if (!rev && n == 1 && reqs[0].count >= SERVE_FULL_MIN && reqs[0].hop.kind != TW_WEIGHT) {
+    if (!rev && n == 1 && reqs[0].count >= SERVE_FULL_MIN && reqs[0].count <= BLOCK_MAX_WALKS &&
+        reqs[0].hop.kind != TW_WEIGHT) {
         const ServeReq& q = reqs[0];
         WalkArgs a;
         if (fill_args(g, q.count, q.max_len, q.start, q.start_mode, q.start_nodes, q.seed, q.base,
@@ -1015,14 +1022,15 @@ tw_status serve_launch(tw_graph* g, const ServeReq* reqs, int n, void* d_table, 
         return err.code;
     TW_HIP(hipMemcpyAsync(d_table, h_table, sizeof(ServeReqDev) * n, hipMemcpyHostToDevice,
                           g->stream));
-    if (blocks > 0) {
-        const ServeReqDev* tab_d = static_cast<const ServeReqDev*>(d_table);
+    const ServeReqDev* tab_d = static_cast<const ServeReqDev*>(d_table);
+    for (int64_t b0 = 0; b0 < blocks; b0 += BLOCK_MAX_WALKS / 64) {
+        const dim3 grid((unsigned)std::min<int64_t>(blocks - b0, BLOCK_MAX_WALKS / 64));
         if (rev)
-            hipLaunchKernelGGL(k_walk_serve<true>, dim3((unsigned)blocks), dim3(64), 0, g->stream,
-                               a, tab_d, n, d_hops);
+            hipLaunchKernelGGL(k_walk_serve<true>, grid, dim3(64), 0, g->stream, a, tab_d, n, b0,
+                               d_hops);
         else
-            hipLaunchKernelGGL(k_walk_serve<false>, dim3((unsigned)blocks), dim3(64), 0, g->stream,
-                               a, tab_d, n, d_hops);
+            hipLaunchKernelGGL(k_walk_serve<false>, grid, dim3(64), 0, g->stream, a, tab_d, n, b0,
+                               d_hops);
     }
     TW_HIP(hipGetLastError());
     return TW_OK;
