@@ -12,10 +12,9 @@
 namespace tw {
 namespace {
 
-// Fill every output slot with the padding values, fully coalesced; the walk
-// kernels then write only the slots their walks reach. (Padding inside the
-// walk kernel, block by block, measured slower: the stores compete with the
-// walks' dependent gathers.)
+// Fill every output slot with the padding values, fully coalesced, for the
+// dispatches whose walks write only the slots they reach, and for walk blocks
+// where their own padding takes longer (blocks_pad).
 __global__ void k_fill_outputs(int32_t* __restrict__ nodes, int64_t* __restrict__ ts,
                                int64_t n) {
     fill_span(nodes, ts, 0, n, (int64_t)blockIdx.x * blockDim.x + threadIdx.x,
@@ -422,7 +421,7 @@ k_walk_full(const WalkArgs a) {
     b.len = a.len;
     b.range_flag = &a.err[0];
     b.cap_count = &a.err[2];
-    b.pad = true;
+    b.pad = !a.pre_filled;
     walk_block<HK, SK, REV, false>(a, b, lds);
 }
 
@@ -510,7 +509,7 @@ constexpr int SERVE_MAX_REQ = 1024;
 struct ServeReqDev {
     int64_t block0, count;  // first block of the launch, walks
     uint64_t seed, base;
-    int32_t L, start_kind, start_mode, pad;
+    int32_t L, start_kind, start_mode, pre_filled;
     double start_tau;
     HopBias hop;
     const int32_t* start_nodes;
@@ -519,6 +518,15 @@ struct ServeReqDev {
     int32_t* len;
     uint32_t* err;  // the request's own words: [0] start node out of range, [1] trial-cap hits
 };
+
+// the outputs of the requests whose blocks do not pad their rows, request
+// blockIdx.y each
+__global__ void k_fill_requests(const ServeReqDev* __restrict__ reqs) {
+    const ServeReqDev& R = reqs[blockIdx.y];
+    if (R.pre_filled)
+        fill_span(R.nodes, R.ts, 0, R.count * (int64_t)R.L,
+                  (int64_t)blockIdx.x * blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x);
+}
 
 // REV: backward requests on the in-view. Before, lanes took walks of any
 // request from a work queue (per-lane parameters, about 180 VGPRs held to 3
@@ -550,7 +558,7 @@ k_walk_serve(const WalkArgs a, const ServeReqDev* __restrict__ reqs, int nreq, i
     b.len = R.len;
     b.range_flag = R.err;
     b.cap_count = R.err + 1;
-    b.pad = true;
+    b.pad = R.pre_filled == 0;
     const int32_t len = walk_block<-1, -1, REV, false>(a, b, lds);
     // hops of the launch: one atomic a block
     int32_t hops = len > 1 ? len - 1 : 0;
@@ -628,19 +636,41 @@ tw_status fill_args(tw_graph* g, int64_t num_walks, int32_t L, const tw_bias& sb
     return TW_OK;
 }
 
+// workgroups of a fill of `slots` slots, at most `most`
+constexpr int64_t FILL_BLOCKS = 8192;
+unsigned fill_grid(int64_t slots, int64_t most) {
+    return (unsigned)std::max<int64_t>(
+        std::min<int64_t>(ceil_div(slots, 4 * WALK_THREADS), most), 1);
+}
+
 void launch_fill(tw_graph* g, int32_t* nodes, int64_t* ts, int64_t slots) {
-    hipLaunchKernelGGL(k_fill_outputs,
-                       dim3((unsigned)std::max<int64_t>(
-                           std::min<int64_t>(ceil_div(slots, 4 * WALK_THREADS), 8192), 1)),
-                       dim3(WALK_THREADS), 0, g->stream, nodes, ts, slots);
+    hipLaunchKernelGGL(k_fill_outputs, dim3(fill_grid(slots, FILL_BLOCKS)), dim3(WALK_THREADS), 0,
+                       g->stream, nodes, ts, slots);
 }
 
 // Most walks one launch of walk blocks takes: a launch holds fewer than 2^32
 // threads (a batch's grid is rounded up to eight stretches of 64 walks a bias).
 constexpr int64_t BLOCK_MAX_WALKS = (1ll << 32) - 8 * 64 * (TW_MAX_BIASES + 1);
 
-// the full-walk kernel; it writes whole rows, padding included
-tw_status full_walks(tw_graph* g, const WalkArgs& a, bool rev, Error& err) {
+// Whether `blocks` walk blocks pad their own rows (of L slots), or the outputs
+// are filled in a launch of their own first. A block's padding is one
+// wavefront's work after its longest walk (about 10 GB/s of it), the fill is the
+// whole chip's: in few blocks the padding of wide rows is a serial tail (64 linear
+// walks of 10,001 slots 341 us, filled first 58; 1,000 of 1,000 128 and 61; of
+// 80 slots 63 and 60). With a wavefront on most SIMDs it hides under other
+// blocks' walks while the outputs fit the 256 MB last-level cache (64,000 of
+// 160 89 and 99; 256,000 of 500 513 and 404). Walks end after a few hops, so
+// the slots that are then written twice are few.
+constexpr int64_t PAD_MAX_L = 96, PAD_MIN_BLOCKS = 600, PAD_MAX_SLOTS = 320 << 10;
+bool blocks_pad(int64_t blocks, int64_t L) {
+    return L <= PAD_MAX_L || (blocks > PAD_MIN_BLOCKS && blocks <= PAD_MAX_SLOTS / L);
+}
+
+// the full-walk kernel, after a fill of the outputs where its blocks do not
+// pad their rows
+tw_status full_walks(tw_graph* g, WalkArgs a, bool rev, Error& err) {
+    a.pre_filled = !blocks_pad(ceil_div(a.num_walks, 64), a.L);
+    if (a.pre_filled) launch_fill(g, a.nodes, a.ts, a.num_walks * (int64_t)a.L);
     const dim3 grid((unsigned)ceil_div(a.num_walks, 64));
     with_kinds(a.hop.kind, a.start_kind, [&](auto h, auto st) {
         with_direction(rev, decltype(h)::value, [&](auto r) {
@@ -671,10 +701,10 @@ tw_status batch_blocks(tw_graph* g, const WalkArgs& a, const QueueArgs& q, Error
     // (about 8 us, the time to fill 4M slots).
     const unsigned long long* gaps = nullptr;
     bool pre_filled = false;
-    if (!q.row && slots >= W * (int64_t)a.L) {
+    if (!q.row && slots >= W * (int64_t)a.L && blocks_pad(ceil_div(W, 64), a.L)) {
         const int64_t used = W * (int64_t)a.L;
         if (slots > used) launch_fill(g, a.nodes + used, a.ts + used, slots - used);
-    } else if (q.row && slots >= BATCH_CHECK_SLOTS) {
+    } else if (q.row && slots >= BATCH_CHECK_SLOTS && blocks_pad(ceil_div(W, 64), slots / W)) {
         unsigned long long* flag = g->wq.as<unsigned long long>();
         hipLaunchKernelGGL(k_clear_word, dim3(1), dim3(1), 0, s, flag);
         hipLaunchKernelGGL(k_rows_tile,
@@ -1015,6 +1045,12 @@ tw_status serve_launch(tw_graph* g, const ServeReq* reqs, int n, void* d_table, 
         tab[r] = d;
         total += q.count;
     }
+    int64_t fill_slots = 0;  // of the largest request to fill first
+    for (int r = 0; r < n; ++r) {
+        if (blocks_pad(blocks, tab[r].L)) continue;
+        tab[r].pre_filled = 1;
+        fill_slots = std::max(fill_slots, tab[r].count * (int64_t)tab[r].L);
+    }
     WalkArgs a;
     tw_bias none{TW_UNIFORM, 0.0, 1.0, 1.0};
     if (fill_args(g, total, 1, none, TW_START_EDGE, nullptr, 0, 0, n2v, wtau, nullptr, nullptr,
@@ -1023,6 +1059,11 @@ tw_status serve_launch(tw_graph* g, const ServeReq* reqs, int n, void* d_table, 
     TW_HIP(hipMemcpyAsync(d_table, h_table, sizeof(ServeReqDev) * n, hipMemcpyHostToDevice,
                           g->stream));
     const ServeReqDev* tab_d = static_cast<const ServeReqDev*>(d_table);
+    if (fill_slots > 0) {
+        const int64_t most = std::min<int64_t>(std::max(16384 / n, 64), FILL_BLOCKS);
+        hipLaunchKernelGGL(k_fill_requests, dim3(fill_grid(fill_slots, most), (unsigned)n),
+                           dim3(WALK_THREADS), 0, g->stream, tab_d);
+    }
     for (int64_t b0 = 0; b0 < blocks; b0 += BLOCK_MAX_WALKS / 64) {
         const dim3 grid((unsigned)std::min<int64_t>(blocks - b0, BLOCK_MAX_WALKS / 64));
         if (rev)

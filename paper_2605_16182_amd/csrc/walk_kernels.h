@@ -62,6 +62,7 @@ struct WalkArgs {
     int64_t* ts;
     int32_t* len;
     uint32_t* err;  // [0] start node out of range, [2] node2vec trial cap hits
+    bool pre_filled;  // the outputs hold padding already (walk blocks leave theirs out)
 };
 
 // The start of a walk: RNG seed, start bias and mode, start nodes.
