@@ -659,11 +659,19 @@ constexpr int64_t BLOCK_MAX_WALKS = (1ll << 32) - 8 * 64 * (TW_MAX_BIASES + 1);
 // walks of 10,001 slots 341 us, filled first 58; 1,000 of 1,000 128 and 61; of
 // 80 slots 63 and 60). With a wavefront on most SIMDs it hides under other
 // blocks' walks while the outputs fit the 256 MB last-level cache (64,000 of
-// 160 89 and 99; 256,000 of 500 513 and 404). Walks end after a few hops, so
-// the slots that are then written twice are few.
+// 160 89 and 99; 256,000 of 500 513 and 404), and with rows so long that a launch
+// is their bandwidth alone: there the fill's slots and the walks' are written one
+// launch after the other (128,000 of 4,000 1.27 and 1.32 ms). From 4,096 slots on
+// a block pads row by row, at about 27 GB/s, and fewer blocks do, fewest where
+// every row begins on 16 bytes (16,000 of 4,096 203 and 211 us; of 5,001 264 and
+// 242; 32,000 of 5,001 452 and 460). Walks end after a few hops, so the slots that
+// a fill writes in vain are few.
 constexpr int64_t PAD_MAX_L = 96, PAD_MIN_BLOCKS = 600, PAD_MAX_SLOTS = 320 << 10;
+constexpr int64_t PAD_LONG_L = 3072;
 bool blocks_pad(int64_t blocks, int64_t L) {
-    return L <= PAD_MAX_L || (blocks > PAD_MIN_BLOCKS && blocks <= PAD_MAX_SLOTS / L);
+    if (L <= PAD_MAX_L) return true;
+    if (L >= PAD_FLAT_MAX_L) return blocks > (L % 4 == 0 ? 192 : 400);
+    return blocks > PAD_MIN_BLOCKS && (L >= PAD_LONG_L || blocks <= PAD_MAX_SLOTS / L);
 }
 
 // the full-walk kernel, after a fill of the outputs where its blocks do not

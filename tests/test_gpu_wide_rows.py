@@ -1,5 +1,5 @@
 """Rows that walk blocks pad themselves and rows that are filled first: widths
-on both sides of the line (97 slots; more blocks than most SIMDs hold; outputs
+on both sides of the line (96 slots; more blocks than most SIMDs hold; outputs
 past the last-level cache), plain, allocation-free, backward, batched and served.
 Against the queue dispatch and the one-thread-per-walk batch, bit for bit, and
 nothing outside the rows."""
@@ -10,9 +10,13 @@ from gpu_util import gpu_or_skip, to_dev
 
 pytestmark = pytest.mark.gpu
 
-# (walks, width): blocks 1, 2, 600 and 601, and 327,680 slots a lane's worth
+# (walks, width): blocks 1, 2, 600 and 601, and 327,680 slots a lane's worth;
+# long rows over 600 blocks and 601, and from 4,096 slots on over 192 and 193, or
+# 400 and 401
 SHAPES = [(1, 96), (1, 97), (65, 96), (65, 99), (65, 100), (65, 5000), (3000, 300), (38_400, 100),
-          (38_401, 100), (40_000, 523), (40_000, 525), (209_000, 100), (210_000, 101)]
+          (38_401, 100), (40_000, 523), (40_000, 525), (209_000, 100), (210_000, 101),
+          (38_401, 3071), (38_401, 3072), (12_288, 4096), (12_289, 4096),
+          (25_600, 4097), (25_601, 4097)]
 
 
 def _graph(torch, tw, directed):
