@@ -291,8 +291,9 @@ __device__ __forceinline__ Pick pick_last(const int32_t* __restrict__ n_dst, con
 __device__ __forceinline__ void computed_here(uint64_t& x) { asm volatile("" : "+v"(x)); }
 
 // The walks of block b, by one wavefront (b.n <= 64). RAGGED: per-walk limits
-// and rows. Returns the length of the lane's walk.
-template <int HK, int SK, bool REV, bool RAGGED>
+// and rows. NEST (node2vec): a lane whose trial was rejected tries again at once,
+// and the others wait for it. Returns the length of the lane's walk.
+template <int HK, int SK, bool REV, bool RAGGED, bool NEST = false>
 __device__ __forceinline__ int32_t walk_block(const WalkArgs& a, const WalkBlock& b, BlockLds& m) {
     const int lane = threadIdx.x & 63;
     const HopBias hb = fixed_hop<HK>(b.hop);
@@ -359,11 +360,16 @@ __device__ __forceinline__ int32_t walk_block(const WalkArgs& a, const WalkBlock
                             hb.tau > 0.0 ? hb.tau : 1.0, group_ts(a.ng, a.fence, r, c.c0), c.t_hi,
                             d);
         } else if (n2v) {
-            const uint32_t i = exp_draw(law, d.x0);
-            p = edge_of_group(a.ng, a.n_dst, c.c1, c.end, REV ? c.c1 - 1 - i : c.c0 + i, d, REV);
-            // the edge prev -> candidate (backward: candidate -> prev of the
-            // graph, which is prev -> candidate of the in-view)
-            take = n2v_accept(a, hb, d.x2, prev, p.dst);
+            while (true) {
+                const uint32_t i = exp_draw(law, d.x0);
+                p = edge_of_group(a.ng, a.n_dst, c.c1, c.end, REV ? c.c1 - 1 - i : c.c0 + i, d,
+                                  REV);
+                // the edge prev -> candidate (backward: candidate -> prev of the
+                // graph, which is prev -> candidate of the in-view)
+                take = n2v_accept(a, hb, d.x2, prev, p.dst);
+                if (!NEST || take || trial + 1 == N2V_MAX_TRIALS) break;
+                d = philox(id, (uint64_t)(len - 1), ++trial, sp.seed);
+            }
         } else {
             p = pick_node(a.ng, a.n_dst, a.n_ts, c.c0, c.c1, c.end, hb.kind, hb.tau, c.t_lo,
                           c.t_hi, d, REV);
@@ -404,7 +410,7 @@ __device__ __forceinline__ int32_t walk_block(const WalkArgs& a, const WalkBlock
 
 // The full-walk dispatch (Sec. "The Full-Walk Baseline"), forward and (REV, on
 // the in-view) backward: contiguous blocks, a workgroup of one wavefront each.
-template <int HK, int SK, bool REV>
+template <int HK, int SK, bool REV, bool NEST = false>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4)))
 k_walk_full(const WalkArgs a) {
     __shared__ BlockLds lds;
@@ -422,7 +428,7 @@ k_walk_full(const WalkArgs a) {
     b.range_flag = &a.err[0];
     b.cap_count = &a.err[2];
     b.pad = !a.pre_filled;
-    walk_block<HK, SK, REV, false>(a, b, lds);
+    walk_block<HK, SK, REV, false, NEST>(a, b, lds);
 }
 
 __global__ void k_clear_word(unsigned long long* p) { *p = 0; }
@@ -674,17 +680,36 @@ bool blocks_pad(int64_t blocks, int64_t L) {
     return blocks > PAD_MIN_BLOCKS && (L >= PAD_LONG_L || blocks <= PAD_MAX_SLOTS / L);
 }
 
+// Whether node2vec walks of at most L nodes retry rejected trials at once
+// (NEST). Interleaved with other lanes' next hops a retry costs a whole
+// iteration, the search of a hop included, as long as some lane begins one: over
+// many hops a lane's trials even out and the block ends sooner, over two to six
+// hops its unluckiest lane sets the pace (50,000 walks of 4 nodes, p = 2, q = 1/2:
+// 84 us, nested 71; of 8 139 and 134; of 12 166 and 180). Once the launch fills the
+// chip, wavefronts in flight decide (76 VGPRs, nested 82; 1.5M walks of 8 nodes
+// 0.74 and 0.87 ms, 400,000 of 4 0.18 and 0.16), and with few blocks seven nodes
+// are many already (1,000 walks of 8 94 and 98 us).
+bool n2v_nested(int64_t blocks, int64_t L) {
+    if (L <= 6) return blocks <= (L == 4 ? 8192 : 2048);
+    return L <= 8 && blocks > 256 && blocks <= 1600;
+}
+
 // the full-walk kernel, after a fill of the outputs where its blocks do not
 // pad their rows
 tw_status full_walks(tw_graph* g, WalkArgs a, bool rev, Error& err) {
     a.pre_filled = !blocks_pad(ceil_div(a.num_walks, 64), a.L);
     if (a.pre_filled) launch_fill(g, a.nodes, a.ts, a.num_walks * (int64_t)a.L);
     const dim3 grid((unsigned)ceil_div(a.num_walks, 64));
+    const bool nest = n2v_nested(grid.x, a.L);
     with_kinds(a.hop.kind, a.start_kind, [&](auto h, auto st) {
         with_direction(rev, decltype(h)::value, [&](auto r) {
-            hipLaunchKernelGGL((k_walk_full<decltype(h)::value, decltype(st)::value,
-                                            decltype(r)::value>),
-                               grid, dim3(64), 0, g->stream, a);
+            constexpr int HK = decltype(h)::value, SK = decltype(st)::value;
+            constexpr bool REV = decltype(r)::value;
+            if (HK == TW_NODE2VEC && nest)
+                hipLaunchKernelGGL((k_walk_full<HK, SK, REV, HK == TW_NODE2VEC>), grid, dim3(64), 0,
+                                   g->stream, a);
+            else
+                hipLaunchKernelGGL((k_walk_full<HK, SK, REV>), grid, dim3(64), 0, g->stream, a);
         });
     });
     TW_HIP(hipGetLastError());
