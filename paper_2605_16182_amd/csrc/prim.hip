@@ -866,12 +866,6 @@ hipError_t radix_sort_pairs(uint64_t* keys, uint64_t* pay, int64_t n, int bits, 
     return radix_sort_impl<uint64_t>(keys, nullptr, pay, keys, nullptr, pay, n, 0, bits, ws, s);
 }
 
-hipError_t radix_sort_u32(uint32_t* keys, uint32_t* vals, int64_t n, int bit_lo, int bit_hi,
-                          Workspace& ws, hipStream_t s) {
-    return radix_sort_impl<uint32_t>(keys, vals, nullptr, keys, vals, nullptr, n, bit_lo, bit_hi,
-                                     ws, s);
-}
-
 hipError_t radix_sort_u32_kv(const uint32_t* kin, const uint32_t* vin, const uint64_t* win,
                              uint32_t* kout, uint32_t* vout, uint64_t* wout, int64_t n, int bit_lo,
                              int bit_hi, Workspace& ws, hipStream_t s) {

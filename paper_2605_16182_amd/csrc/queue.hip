@@ -89,8 +89,7 @@ struct RowRing {
 // or after t, listed from the latest, so every pick index is mirrored.
 __device__ __forceinline__ bool back_pick(const WalkArgs& a, const HopBias& hb, uint64_t seed,
                                           const NodeRec& r, uint32_t hi, uint64_t id,
-                                          uint64_t hop, int32_t prev, Pick& p, int32_t& nx,
-                                          uint32_t* cap_count = nullptr) {
+                                          uint64_t hop, int32_t prev, Pick& p, int32_t& nx) {
     const uint32_t end = hi < r.ge ? a.ng[hi].first : r.ee;  // the candidates' edges end
     const bool rate = reads_first_ts(hb.kind);
     const int64_t t_lo = rate ? group_ts(a.ng, a.fence, r, r.gb) : 0;
@@ -110,7 +109,7 @@ __device__ __forceinline__ bool back_pick(const WalkArgs& a, const HopBias& hb, 
         nx = p.dst;
         if (n2v_accept(a, hb, d.x2, prev, nx)) return true;
     }
-    atomicAdd(cap_count ? cap_count : &a.err[2], 1u);
+    atomicAdd(&a.err[2], 1u);
     return false;
 }
 
@@ -615,17 +614,13 @@ tw_status coop_walks(tw_graph* g, const WalkArgs& a, Error& err) {
     return TW_OK;
 }
 
-// compute units and the workgroups of k_walk_queue one of them holds at
-// once, queried once per graph (host-side queries only, so a walk launch can
-// be captured in a graph afterwards)
+// compute units, queried once per graph (a host-side query only, so a walk
+// launch can be captured in a graph afterwards)
 tw_status queue_shape(tw_graph* g, Error& err) {
     if (g->cu_count) return TW_OK;
-    int n = 0, nb = 0;
+    int n = 0;
     TW_HIP(hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, g->device));
-    TW_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_walk_queue<true, -1, -1>,
-                                                         WALK_THREADS, 0));
     g->cu_count = std::max(n, 1);
-    g->queue_bpc_max = std::max(nb, 1);
     return TW_OK;
 }
 
@@ -648,7 +643,7 @@ tw_status queue_walks(tw_graph* g, const WalkArgs& a, const QueueArgs& q0, int b
     hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(64), 0, g->stream, q.counters);
     const int hk = q.n_bias == 1 ? q.bias[0].kind : -1;
     with_kinds(hk, a.start_kind, [&](auto h, auto st) {
-        with_direction(rev, decltype(h)::value, [&](auto r) {
+        with_direction<decltype(h)::value>(rev, [&](auto r) {
             auto kernel =
                 k_walk_queue<true, decltype(h)::value, decltype(st)::value, decltype(r)::value>;
             static const int maxb = resident_bpc(kernel);  // per instantiation
@@ -668,7 +663,7 @@ tw_status batch_full_walk(tw_graph* g, const WalkArgs& a, const QueueArgs& q, Er
                           bool rev) {
     const int hk = q.n_bias == 1 ? q.bias[0].kind : -1;
     with_kinds(hk, a.start_kind, [&](auto h, auto st) {
-        with_direction(rev, decltype(h)::value, [&](auto r) {
+        with_direction<decltype(h)::value>(rev, [&](auto r) {
             hipLaunchKernelGGL((k_walk_queue<false, decltype(h)::value, decltype(st)::value,
                                              decltype(r)::value>),
                                dim3((unsigned)ceil_div(a.num_walks, WALK_THREADS)),

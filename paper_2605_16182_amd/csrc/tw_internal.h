@@ -258,13 +258,9 @@ hipError_t group_starts(int has_last, int64_t last_ts, const int64_t* ts, int64_
                         uint32_t pos_base, uint32_t* g_off, uint32_t* total, Workspace& ws,
                         hipStream_t s, DevBuf* counted = nullptr);
 
-// Stable LSD radix sort of (keys, vals) by bits [bit_lo, bit_hi) of the key.
-// vals may be null. Result ends in keys / vals. The alternate buffers come
-// from the workspace.
-hipError_t radix_sort_u32(uint32_t* keys, uint32_t* vals, int64_t n, int bit_lo, int bit_hi,
-                          Workspace& ws, hipStream_t s);
-// Stable sort of 32- or 64-bit keys by their low `bits` bits, carrying a
-// 64-bit payload, in place.
+// Stable LSD radix sort of 32- or 64-bit keys by their low `bits` bits,
+// carrying a 64-bit payload, in place. The alternate buffers come from the
+// workspace.
 hipError_t radix_sort_pairs(uint32_t* keys, uint64_t* pay, int64_t n, int bits, Workspace& ws,
                             hipStream_t s);
 hipError_t radix_sort_pairs(uint64_t* keys, uint64_t* pay, int64_t n, int bits, Workspace& ws,
@@ -391,7 +387,7 @@ struct tw_graph {
     // queue dispatch: slice counters; compute units; the dispatch AUTO runs
     // (0: full-walk until tw_autotune chooses) and the queue's workgroups per CU
     tw::DevBuf wq;
-    int cu_count = 0, queue_bpc_max = 0;
+    int cu_count = 0;
     int auto_dispatch = 0;
     int auto_bpc = 0;
 

@@ -702,15 +702,17 @@ tw_status full_walks(tw_graph* g, WalkArgs a, bool rev, Error& err) {
     const dim3 grid((unsigned)ceil_div(a.num_walks, 64));
     const bool nest = n2v_nested(grid.x, a.L);
     with_kinds(a.hop.kind, a.start_kind, [&](auto h, auto st) {
-        with_direction(rev, decltype(h)::value, [&](auto r) {
-            constexpr int HK = decltype(h)::value, SK = decltype(st)::value;
-            constexpr bool REV = decltype(r)::value;
-            if (HK == TW_NODE2VEC && nest)
-                hipLaunchKernelGGL((k_walk_full<HK, SK, REV, HK == TW_NODE2VEC>), grid, dim3(64), 0,
-                                   g->stream, a);
-            else
-                hipLaunchKernelGGL((k_walk_full<HK, SK, REV>), grid, dim3(64), 0, g->stream, a);
-        });
+        constexpr int HK = decltype(h)::value, SK = decltype(st)::value;
+        // (these walks share one hop kind)
+        if constexpr (HK >= 0)
+            with_direction<HK>(rev, [&](auto r) {
+                constexpr bool REV = decltype(r)::value;
+                if (HK == TW_NODE2VEC && nest)
+                    hipLaunchKernelGGL((k_walk_full<HK, SK, REV, HK == TW_NODE2VEC>), grid, dim3(64),
+                                       0, g->stream, a);
+                else
+                    hipLaunchKernelGGL((k_walk_full<HK, SK, REV>), grid, dim3(64), 0, g->stream, a);
+            });
     });
     TW_HIP(hipGetLastError());
     return TW_OK;
@@ -756,7 +758,7 @@ tw_status batch_blocks(tw_graph* g, const WalkArgs& a, const QueueArgs& q, Error
         const dim3 grid((unsigned)(only >= 0 ? stretches
                                              : ceil_div(stretches, NUM_XCD) * NUM_XCD * nb));
         with_kinds(hk, a.start_kind, [&](auto h, auto st) {
-            with_direction(rev, decltype(h)::value, [&](auto r) {
+            with_direction<decltype(h)::value>(rev, [&](auto r) {
                 hipLaunchKernelGGL((k_walk_batch<decltype(h)::value, decltype(st)::value,
                                                  decltype(r)::value>),
                                    grid, dim3(64), 0, s, a, q, pre_filled, gaps, only);

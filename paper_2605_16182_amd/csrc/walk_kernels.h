@@ -183,12 +183,10 @@ __device__ __forceinline__ bool n2v_accept(const WalkArgs& a, const HopBias& hb,
 
 // The pick of hop `hop` among groups [gc, r.ge) of node cur (previous node
 // prev): the hop bias, or node2vec's rejection loop. Returns false when
-// node2vec exhausts its trials (the walk ends; counted in *cap_count, the
-// graph's counter word when null).
+// node2vec exhausts its trials (the walk ends and is counted).
 __device__ __forceinline__ bool hop_pick(const WalkArgs& a, const HopBias& hb, uint64_t seed,
                                          const NodeRec& r, uint32_t gc, uint64_t id, uint64_t hop,
-                                         int32_t prev, Pick& p, int32_t& nx,
-                                         uint32_t* cap_count = nullptr) {
+                                         int32_t prev, Pick& p, int32_t& nx) {
     if (hb.kind == TW_WEIGHT) {
         const Draw d = philox(id, hop, 0, seed);
         p = pick_weight(a.ng, a.n_dst, a.cw, r.gb, gc, r.ge, r.ee, hb.tau > 0.0 ? hb.tau : 1.0,
@@ -212,7 +210,7 @@ __device__ __forceinline__ bool hop_pick(const WalkArgs& a, const HopBias& hb, u
         nx = p.dst;
         if (n2v_accept(a, hb, d.x2, prev, nx)) return true;
     }
-    atomicAdd(cap_count ? cap_count : &a.err[2], 1u);
+    atomicAdd(&a.err[2], 1u);
     return false;
 }
 
@@ -289,13 +287,13 @@ void with_kinds(int hk, int sk, F&& f) {
     }
 }
 
-// Calls f with the direction as a compile-time constant. Backward walks
-// never take the weight-based picker (refused before any launch), so its
-// backward instantiations are not built.
-template <typename F>
-void with_direction(bool rev, int hk, F&& f) {
+// Calls f with the direction as a compile-time constant, for hop kind HK.
+// Backward walks never take the weight-based picker (refused before any
+// launch), so its backward instantiations are not built.
+template <int HK, typename F>
+void with_direction(bool rev, F&& f) {
     if (!rev) f(std::false_type{});
-    else if (hk != TW_WEIGHT) f(std::true_type{});
+    else if constexpr (HK != TW_WEIGHT) f(std::true_type{});
 }
 
 // Whether the queue kernels write whole output rows themselves (four slots
