@@ -141,11 +141,18 @@ __global__ void k_scan_down(const In* in, V* out, int64_t n, const V* __restrict
 template <typename V>
 __global__ void k_set(V* p, V v) { *p = v; }
 
-// Scans of up to SCAN_ONE_MAX elements in one launch of one workgroup, a
+// Scans of up to scan_one_max elements in one launch of one workgroup, a
 // thread its own consecutive elements: for these the two launches above are
-// launch time (about 6 us each in a small ingest, which makes nine scans).
+// launch time. Further up the one workgroup's strided accesses cost more than
+// the launch saved, sooner where the sums are 64-bit (with the caller's
+// read-back: 4,096 elements 28 us, two launches 33; 7,168 31 and 33; 8,192 36 and
+// 33; 16,384 49 and 33). 32-bit sums, in an ingest: 4,000 undirected edges 229 us,
+// 240 with the line at 7 x 1024; 60,000 282, 311 with it at 16 x 1024.
 constexpr int SCAN_ONE_THREADS = 1024;
-constexpr int64_t SCAN_ONE_MAX = 16 * SCAN_ONE_THREADS;
+template <typename V>
+constexpr int64_t scan_one_max() {
+    return (sizeof(V) == 8 ? 7 : 12) * SCAN_ONE_THREADS;
+}
 
 // exclusive scan of one value per thread over a 1024-thread block
 template <typename V>
@@ -523,7 +530,9 @@ k_rs_scatter(const K* __restrict__ keys, const uint32_t* __restrict__ vals,
 // above do and exchanges them through LDS. A small sort is launches otherwise:
 // four a pass, two or three passes, two sorts an ingest (2,000 undirected
 // edges into a 400,000-record window, with the one-launch scans: 59 launches and
-// 397 us an ingest and its walks -> 39 and 327).
+// 397 us an ingest and its walks -> 39 and 327). RS_ONE is what its registers and
+// 48 KB of LDS hold; up to there it is the faster form (an ingest of 4,096
+// unsorted records 191 us, through tiles 222; of 1,000 165 and 185).
 // W64, PACK as in k_rs_scatter.
 constexpr int RS_ONE_THREADS = 1024;
 constexpr int RS_ONE_ITEMS = 4;
@@ -770,7 +779,7 @@ hipError_t scan_core(const In* in, V* out, int64_t n, V* total, V* part, hipStre
         if (total) hipLaunchKernelGGL(k_set<V>, dim3(1), dim3(1), 0, s, total, (V)0);
         return hipGetLastError();
     }
-    if (n <= SCAN_ONE_MAX) {
+    if (n <= scan_one_max<V>()) {
         hipLaunchKernelGGL((k_scan_one<In, V>), dim3(1), dim3(SCAN_ONE_THREADS), 0, s, in, out, n,
                            total);
         return hipGetLastError();
@@ -791,7 +800,7 @@ hipError_t scan_core(const In* in, V* out, int64_t n, V* total, V* part, hipStre
 template <typename In, typename V>
 hipError_t scan_exclusive(const In* in, V* out, int64_t n, V* total, DevBuf& part_buf,
                           hipStream_t s) {
-    if (n > SCAN_ONE_MAX) {
+    if (n > scan_one_max<V>()) {
         const hipError_t e = ensure(part_buf, sizeof(V) * (ceil_div(n, SCAN_TILE) + 1), s);
         if (e != hipSuccess) return e;
     }
@@ -817,7 +826,7 @@ hipError_t scan_exclusive_u32x4(const uint32_t* const in[4], uint32_t* const out
             if (total[y]) hipLaunchKernelGGL(k_set<uint32_t>, dim3(1), dim3(1), 0, s, total[y], 0u);
         return hipGetLastError();
     }
-    if (n <= SCAN_ONE_MAX) {
+    if (n <= scan_one_max<uint32_t>()) {
         hipLaunchKernelGGL(k_scan4_one, dim3(4), dim3(SCAN_ONE_THREADS), 0, s, a, n, n_dev);
         return hipGetLastError();
     }
