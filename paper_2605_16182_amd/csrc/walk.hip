@@ -66,7 +66,7 @@ struct WalkBlock {
     const int64_t* rows;
     int64_t out_slots;
     uint32_t* bad_flag;
-    bool pad;  // the block pads its rows (else the outputs were pre-filled)
+    bool pad;  // the block pads its rows, of L slots (else the outputs were pre-filled)
 
     // nodes and ts 16-byte aligned: four slots leave as vectors
     __device__ __forceinline__ bool vec() const {
@@ -399,12 +399,9 @@ __device__ __forceinline__ int32_t walk_block(const WalkArgs& a, const WalkBlock
         return len;
     }
     // 16 lanes a row
-    for (int k = lane >> 4; k < b.n; k += 4) {
-        const int64_t wk = b.w0 + k * b.stride;
-        const int64_t rk = RAGGED && b.rows ? b.rows[wk] : wk * (int64_t)b.L;
-        const int32_t wid = RAGGED && b.rows && b.limits ? b.limits[wk] : b.L;
-        pad_row(b.nodes, b.ts, rk, m.at[k], wid, b.vec(), lane & 15, 16);
-    }
+    for (int k = lane >> 4; k < b.n; k += 4)
+        pad_row(b.nodes, b.ts, (b.w0 + k * b.stride) * (int64_t)b.L, m.at[k], b.L, b.vec(), lane & 15,
+                16);
     return len;
 }
 
@@ -431,32 +428,6 @@ k_walk_full(const WalkArgs a) {
     walk_block<HK, SK, REV, false, NEST>(a, b, lds);
 }
 
-__global__ void k_clear_word(unsigned long long* p) { *p = 0; }
-
-// Whether the rows of a batch lie one after the other over all of its slots:
-// sets *gaps when some row does not end where the next begins (or a limit is
-// out of range).
-__global__ void k_rows_tile(const int64_t* __restrict__ row, const int32_t* __restrict__ max_len,
-                            int32_t L, int64_t n, int64_t out_slots, unsigned long long* gaps) {
-    bool bad = false;
-    for (int64_t i = (int64_t)blockIdx.x * WALK_THREADS + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * WALK_THREADS) {
-        const int32_t lim = max_len ? max_len[i] : L;
-        const uint64_t end = (uint64_t)(i + 1 < n ? row[i + 1] : out_slots);
-        bad |= lim < 1 || lim > L || (uint64_t)row[i] + (uint64_t)lim != end ||
-               (i == 0 && row[0] != 0);
-    }
-    if (__ballot(bad) != 0 && (threadIdx.x & 63) == 0) atomicOr(gaps, 1ull);
-}
-
-// k_fill_outputs when *gaps is set
-__global__ void k_fill_gaps(int32_t* __restrict__ nodes, int64_t* __restrict__ ts, int64_t n,
-                            const unsigned long long* __restrict__ gaps) {
-    if (*gaps == 0) return;
-    fill_span(nodes, ts, 0, n, (int64_t)blockIdx.x * blockDim.x + threadIdx.x,
-              (int64_t)gridDim.x * blockDim.x);
-}
-
 // A batch in walk blocks. With several biases assigned by walk id (id mod
 // n_bias), a block takes the walks of one bias of a stretch of n_bias x 64
 // walks, so its wavefront runs one picker: lanes of six different biases ran
@@ -466,12 +437,11 @@ __global__ void k_fill_gaps(int32_t* __restrict__ nodes, int64_t* __restrict__ t
 // biases on a work queue and a fill pass before it, 10.0 with one launch of
 // this kernel at 128 VGPRs, 7.4 with one launch a bias); else the blocks of a
 // stretch go to one XCD (every eighth workgroup), where the lines that
-// their rows share meet in its L2. The blocks pad their rows unless
-// pre_filled, or (gaps given) *gaps is set.
+// their rows share meet in its L2. The blocks pad their rows unless the outputs
+// are pre_filled.
 template <int HK, int SK, bool REV>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4)))
-k_walk_batch(const WalkArgs a, const QueueArgs q, bool pre_filled,
-             const unsigned long long* __restrict__ gaps, int only) {
+k_walk_batch(const WalkArgs a, const QueueArgs q, int only) {
     __shared__ BlockLds lds;
     const int nb = q.n_bias;
     WalkBlock b;
@@ -497,7 +467,7 @@ k_walk_batch(const WalkArgs a, const QueueArgs q, bool pre_filled,
     b.rows = q.row;
     b.out_slots = q.out_slots;
     b.bad_flag = &a.err[3];
-    b.pad = gaps ? *gaps == 0 : !pre_filled;
+    b.pad = !a.pre_filled;
     walk_block<HK, SK, REV, true>(a, b, lds);
 }
 
@@ -718,40 +688,25 @@ tw_status full_walks(tw_graph* g, WalkArgs a, bool rev, Error& err) {
     return TW_OK;
 }
 
-// slots from which a batch with given rows checks whether they cover all of
-// them instead of filling them first
-constexpr int64_t BATCH_CHECK_SLOTS = 4 << 20;
-
 // A batch whose biases go by walk id, in walk blocks.
-tw_status batch_blocks(tw_graph* g, const WalkArgs& a, const QueueArgs& q, Error& err, bool rev) {
+tw_status batch_blocks(tw_graph* g, WalkArgs a, const QueueArgs& q, Error& err, bool rev) {
     if (queue_shape(g, err) != TW_OK) return err.code;
     hipStream_t s = g->stream;
-    // whichever batch comes first: a later one may be under graph capture,
-    // which must not allocate
+    // whichever batch comes first: a later one may run on the queue under graph
+    // capture, which must not allocate
     TW_HIP(ensure(g->wq, sizeof(unsigned long long) * QUEUE_SLICES, s));
-    const int64_t W = a.num_walks, slots = q.out_slots;
-    // The blocks pad their own rows where the rows cover every slot: rows of L
-    // slots known here, given ones checked on the device. Small outputs are
-    // filled at once: the check and the conditional fill are two more launches
-    // (about 8 us, the time to fill 4M slots).
-    const unsigned long long* gaps = nullptr;
-    bool pre_filled = false;
-    if (!q.row && slots >= W * (int64_t)a.L && blocks_pad(ceil_div(W, 64), a.L)) {
-        const int64_t used = W * (int64_t)a.L;
-        if (slots > used) launch_fill(g, a.nodes + used, a.ts + used, slots - used);
-    } else if (q.row && slots >= BATCH_CHECK_SLOTS && blocks_pad(ceil_div(W, 64), slots / W)) {
-        unsigned long long* flag = g->wq.as<unsigned long long>();
-        hipLaunchKernelGGL(k_clear_word, dim3(1), dim3(1), 0, s, flag);
-        hipLaunchKernelGGL(k_rows_tile,
-                           dim3((unsigned)std::min<int64_t>(ceil_div(W, WALK_THREADS), 2048)),
-                           dim3(WALK_THREADS), 0, s, q.row, q.max_len, a.L, W, slots, flag);
-        hipLaunchKernelGGL(k_fill_gaps, dim3(8192), dim3(WALK_THREADS), 0, s, a.nodes, a.ts, slots,
-                           flag);
-        gaps = flag;
-    } else {
+    // Rows of L slots that cover the outputs are padded by their blocks, as plain
+    // walks' are. Given rows are filled first: whether they cover every slot
+    // would have to be checked on the device, and checked and padded by the blocks
+    // they took longer at every size (1M linear walks of 5-120 slots 732 us, filled
+    // first 665; 8M exponential ones 5.80 and 5.35 ms; 250,000 of 1-60 slots with
+    // gaps between the rows 151 and 101 us).
+    const int64_t W = a.num_walks, slots = q.out_slots, used = W * (int64_t)a.L;
+    a.pre_filled = q.row || slots < used || !blocks_pad(ceil_div(W, 64), a.L);
+    if (a.pre_filled)
         launch_fill(g, a.nodes, a.ts, slots);
-        pre_filled = true;
-    }
+    else if (slots > used)
+        launch_fill(g, a.nodes + used, a.ts + used, slots - used);
     const int nb = q.n_bias;
     const int64_t stretches = ceil_div(W, (int64_t)64 * nb);
     auto launch = [&](int hk, int only) {
@@ -761,7 +716,7 @@ tw_status batch_blocks(tw_graph* g, const WalkArgs& a, const QueueArgs& q, Error
             with_direction<decltype(h)::value>(rev, [&](auto r) {
                 hipLaunchKernelGGL((k_walk_batch<decltype(h)::value, decltype(st)::value,
                                                  decltype(r)::value>),
-                                   grid, dim3(64), 0, s, a, q, pre_filled, gaps, only);
+                                   grid, dim3(64), 0, s, a, q, only);
             });
         });
     };

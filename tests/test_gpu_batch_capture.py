@@ -12,7 +12,8 @@ BIASES = [("uniform", 0.0, 1.0, 1.0), ("linear", 0.0, 1.0, 1.0)]
 
 
 @pytest.mark.parametrize("warm", ["blocks", "queue"])
-def test_large_ragged_batch_after_a_small_one(warm):
+@pytest.mark.parametrize("recorded", ["blocks", "queue"])
+def test_large_ragged_batch_after_a_small_one(warm, recorded):
     torch, tw = gpu_or_skip()
     rng = np.random.default_rng(6)
     V, n, W, L = 400, 6000, 300_000, 30
@@ -22,22 +23,23 @@ def test_large_ragged_batch_after_a_small_one(warm):
                    rng.integers(0, V, n).astype(np.int32),
                    rng.integers(0, 3000, n).astype(np.int64))
     lim = torch.from_numpy(rng.integers(1, L + 1, W).astype(np.int32)).cuda()
-    idx = torch.zeros(100, dtype=torch.uint8, device="cuda")
+    idx = torch.zeros(W, dtype=torch.uint8, device="cuda")  # biases per walk: the work queue
     torch.cuda.synchronize()
     g.ingest_batch(*edges)
     rows = g.row_offsets(lim)
-    assert rows[1] >= 4 << 20  # from here on given rows are checked on the device
     out, want = [(torch.empty(rows[1], dtype=torch.int32, device="cuda"),
                   torch.empty(rows[1], dtype=torch.int64, device="cuda"),
                   torch.empty(W, dtype=torch.int32, device="cuda")) for _ in range(2)]
     g.sample_walks_batch(100, 5, BIASES, bias_idx=idx if warm == "queue" else None)
+    kw = dict(max_lens=lim, bias_idx=idx if recorded == "queue" else None, seed=5, ragged=True,
+              rows=rows)
     held, layout = g.device_bytes(), g.walk_layout()
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph, stream=cap):
-        g.sample_walks_batch(W, L, BIASES, max_lens=lim, seed=5, ragged=True, rows=rows, out=out)
+        g.sample_walks_batch(W, L, BIASES, out=out, **kw)
     assert (g.device_bytes(), g.walk_layout()) == (held, layout)
-    g.sample_walks_batch(W, L, BIASES, max_lens=lim, seed=5, ragged=True, rows=rows, out=want)
+    g.sample_walks_batch(W, L, BIASES, out=want, **kw)
     for _ in range(3):
         for x in out:
             x.fill_(7)

@@ -1,8 +1,8 @@
 """Row starts of a batch that no output can hold: near INT64_MAX the end of the
 row, its start plus the walk's limit, does not fit 64 bits. Such a walk gets
 length 0 and the call that synchronises next reports it; the others are as
-without it. Walk blocks (outputs filled first, and rows checked), the work
-queue (biases given per walk) and one thread per walk."""
+without it. Walk blocks, the work queue (biases given per walk) and one thread
+per walk."""
 import numpy as np
 import pytest
 
