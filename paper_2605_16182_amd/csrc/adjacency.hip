@@ -57,8 +57,13 @@ __device__ __forceinline__ void adj_count(AdjSlot* __restrict__ tab, uint64_t ma
 // table with its count. One atomic per record before: the table of a 50M-record
 // window 29 -> 4.6 ms, 500,000 records down and as many up 338 -> 110 us.
 constexpr int ADJ_ENTRIES = 2048;
-// records from which tiles of 16 a thread fill the chip (fewer: 4 a thread)
-constexpr int64_t ADJ_LARGE = 4 << 20;
+// Records from which a tile takes 16 a thread instead of 4: a larger tile meets
+// more of its repeats, a smaller one leaves fewer compute units idle (skewed
+// sources and destinations, an ingest of b records that evicts as many: b =
+// 100,000 319 us, at 16 a thread 337; 250,000 343 and 342; 500,000 433 and 406;
+// 4M 1.43 and 1.19 ms; evenly spread pairs 200,000 318 and 337, 500,000 363 and
+// 365).
+constexpr int64_t ADJ_LARGE = 3 << 18;
 template <int ITEMS>
 __global__ void __launch_bounds__(AT) k_adj_count(AdjSlot* __restrict__ tab, uint64_t mask,
                                                    const int32_t* __restrict__ src0,
