@@ -121,9 +121,11 @@ def probe_rates(torch, dev):
     return best, copy_best
 
 
+# what the walk kernels are made of; the compiler flags in build.py among it
+# (walk.hip's registers, so its traffic, depend on them)
 WALK_SOURCES = ("paper_2605_16182_amd/csrc/walk.hip", "paper_2605_16182_amd/csrc/walk_kernels.h",
                 "paper_2605_16182_amd/csrc/walk_device.h",
-                "paper_2605_16182_amd/csrc/tw_internal.h")
+                "paper_2605_16182_amd/csrc/tw_internal.h", "paper_2605_16182_amd/build.py")
 TRAFFIC_FILES = {"single": os.path.join(ROOT, "profiles", "walk_traffic_single_100M.txt"),
                  "stream": os.path.join(ROOT, "profiles", "walk_traffic_stream_1B.txt")}
 
@@ -168,7 +170,9 @@ def ingest_bytes(b_in, kept, evicted, jobs):
     (32 B), append them to the timestamp view with its group starts (16 + 4
     B) and to their nodes' runs in the node view with group records (12 + 16
     B), read the sources of the evicted records (4 B), and read and write the
-    record of every node whose run changed (2 x 48 B)."""
+    record of every node whose run changed (2 x 48 B: what an update has to
+    keep; the 64-byte record's copy of the node's last group is the layout's
+    own)."""
     return 16 * b_in + 80 * kept + 4 * evicted + 96 * jobs
 
 
@@ -563,10 +567,11 @@ def run_stream(args, torch, tw, w, dev, gather_rate, copy_bw):
 
 
 def run_mixed(args, torch, tw, w, dev, gather_rate):
-    """Batched mixed walks: one persistent work-queue launch of walks with
-    lengths uniform in [min_len, max_len] and six hop biases (walk id mod 6)
-    on an undirected power-law graph, against the same batch with one thread
-    per walk and no queue."""
+    """Batched mixed walks: a batch of walks with lengths uniform in
+    [min_len, max_len] and six hop biases (walk id mod 6) on an undirected
+    power-law graph, in walk blocks of one bias each, against the same batch on
+    the work queue (the same biases given per walk) and with one thread per
+    walk."""
     import synth
     spec = w["stream"]
     src, dst, ts = spec.all()
@@ -589,16 +594,18 @@ def run_mixed(args, torch, tw, w, dev, gather_rate):
     kw = dict(max_lens=lims, seed=42, ragged=True, rows=rows, out=out)
     res_d = {}
     hops = None
-    for disp in ("full_walk", "queue"):
+    by_walk = (torch.arange(W, device=dev) % len(biases)).to(torch.uint8)
+    forms = {"full_walk": dict(dispatch="full_walk"), "queue": dict(bias_idx=by_walk), "blocks": {}}
+    for disp, form in forms.items():
         for _ in range(max(args.warmup, 1)):
-            g.sample_walks_batch(W, L, biases, dispatch=disp, **kw)
+            g.sample_walks_batch(W, L, biases, **form, **kw)
         evs = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True))
                for _ in range(args.steps)]
         torch.cuda.synchronize()
         t0 = time.perf_counter()
         for a, b in evs:
             a.record()
-            g.sample_walks_batch(W, L, biases, dispatch=disp, **kw)
+            g.sample_walks_batch(W, L, biases, **form, **kw)
             b.record()
         torch.cuda.synchronize()
         wall = time.perf_counter() - t0
@@ -637,7 +644,7 @@ def run_mixed(args, torch, tw, w, dev, gather_rate):
         plain[disp] = {"walk_ms": ms, "walk_hops_per_s": h / (ms * 1e-3)}
     plain["walks"], plain["max_len"], plain["hops"] = Wp, Lp, phops
     plain["sweep"] = dispatch_sweep(torch, g, Wp, Lp, pkw, phops)
-    q = res_d["queue"]
+    q = res_d["blocks"]
     roof = gather_rate / 4 if gather_rate else None
     res = {
         "metric": METRIC, "value": q["walk_hops_per_s"], "unit": "hops/s",
@@ -648,7 +655,7 @@ def run_mixed(args, torch, tw, w, dev, gather_rate):
             "min_len": w["min_len"], "hop_biases": [b[0] if b[0] != "node2vec" else
                                                     f"node2vec({b[2]},{b[3]})" for b in biases],
             "layout": "ragged rows"},
-        "dispatch": "queue",
+        "dispatch": "walk blocks",
         "hops_per_step": hops,
         "batched_vs_plain": res_d,
         "plain_walks_by_dispatch": plain,

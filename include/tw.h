@@ -146,8 +146,9 @@ typedef struct {
 
 /*
  * A batch of walks of uneven lengths and mixed hop biases: biases by walk id
- * (d_bias NULL) run in blocks of walks of one bias, given ones in one
- * persistent launch with a device work queue. Walk i has
+ * (d_bias NULL) run in blocks of 64 walks of one bias, given ones in one
+ * persistent launch with a device work queue (ids that wrap past 2^64 and
+ * batches of about 2^32 walks and more do too). Walk i has
  * RNG id walk_id_base + i, length limit d_max_len[i] (or max_len), hop bias
  * hop_biases[d_bias[i]] (or hop_biases[(walk_id_base + i) mod num_biases]),
  * and writes its nodes and timestamps at d_row[i] (or i * max_len). A walk's
@@ -170,9 +171,12 @@ typedef struct {
     const int64_t* d_row;        /* num_walks row starts (see tw_row_offsets), or NULL */
     int64_t out_slots;           /* slots of d_nodes and d_ts, padded by the call;
                                     0 with d_row NULL: num_walks * max_len */
-    int32_t dispatch;            /* TW_DISPATCH_QUEUE (AUTO means it), or
-                                    TW_DISPATCH_FULL_WALK: one thread per walk in id
-                                    order, rows pre-filled (for comparison) */
+    int32_t dispatch;            /* TW_DISPATCH_AUTO or TW_DISPATCH_QUEUE: as said above,
+                                    blocks or the queue; no more than a hint where
+                                    biases go by walk id, which the queue takes only
+                                    when given in d_bias. TW_DISPATCH_FULL_WALK: one
+                                    thread per walk in id order, rows pre-filled (for
+                                    comparison) */
     int32_t direction;           /* tw_direction (0: forward); backward walks take
                                     no TW_WEIGHT bias */
 } tw_batch_params;
@@ -328,7 +332,8 @@ tw_status tw_row_offsets(tw_graph* g, const int32_t* d_max_len, int64_t n, int64
  * How TW_DISPATCH_AUTO and the cooperative dispatch run (Sec.
  * "Hierarchical Cooperative Scheduling", Sec. "Parameter Tuning"):
  *  dispatch:      what TW_DISPATCH_AUTO runs (FULL_WALK, COOP or QUEUE)
- *  queue_bpc:     queue workgroups per compute unit (0: as many as fit)
+ *  queue_bpc:     queue workgroups per compute unit (0: as many as fit); of
+ *                 batches, those that run on the queue
  *  coop_regroup:  per step, 0 = stable sort of the live walks by node, 1 = none
  *                 (in-order compaction only)
  *  coop_wave_min: lanes of a wavefront at its first lane's node that make it
@@ -373,13 +378,15 @@ tw_status tw_autotune(tw_graph* g, const tw_walk_params* params, int64_t sample_
  * hipMalloc.
  */
 
-/* Most walks one tw_sample_walks_noalloc call takes. */
+/* Most walks one tw_sample_walks_noalloc call takes. Part of its contract only:
+ * nothing in the library is sized by it. */
 #define TW_NOALLOC_MAX_WALKS 262144
 
 /*
  * The walks of tw_sample_walks (the same results), with no device
  * allocation, free or memset: one kernel that keeps a walk's state in
- * registers and on-chip memory, so the call can be captured in a HIP graph.
+ * registers and on-chip memory (after one that fills the outputs, for wide
+ * rows), so the call can be captured in a HIP graph.
  * Arguments and outputs as tw_sample_walks; params->dispatch is ignored.
  * Stream-ordered, no synchronisation; calls on several graphs or streams, and
  * replays of captured calls, may overlap (one graph handle still belongs to
@@ -479,9 +486,9 @@ tw_status tw_server_wait(tw_server* s, uint64_t id, int64_t timeout_us, tw_reque
  * unknown. TW_EINVAL if it has not finished or is unknown. */
 tw_status tw_server_release(tw_server* s, uint64_t id);
 
-/* Copy finished request id's outputs into caller device memory: d_nodes
- * and d_ts num_walks x max_len, d_len num_walks (any pointer may be NULL).
- * Synchronous. TW_EINVAL if the request is unknown or has not finished. */
+/* Copy finished request id's outputs into caller device memory, of the
+ * graph's device or another: d_nodes and d_ts num_walks x max_len, d_len
+ * num_walks (any pointer may be NULL). Synchronous. TW_EINVAL if the request is unknown or has not finished. */
 tw_status tw_server_copy_out(tw_server* s, uint64_t id, int32_t* d_nodes, int64_t* d_ts,
                              int32_t* d_len);
 

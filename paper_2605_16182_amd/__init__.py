@@ -260,8 +260,8 @@ class Graph:
                              start_mode: str = "edge", start_nodes: Optional[torch.Tensor] = None,
                              seed: int = 42, walk_id_base: int = 0):
         """tw_sample_walks_noalloc into the caller's out = (nodes int32[W, L],
-        ts int64[W, L], len int32[W]): the queue dispatch's walks with no
-        device allocation (at most MAX_NOALLOC_WALKS walks)."""
+        ts int64[W, L], len int32[W]): the same walks with no device allocation
+        (at most MAX_NOALLOC_WALKS walks)."""
         W, L = int(num_walks), int(max_len)
         nodes, ts, lens = out
         if start_nodes is not None:
@@ -282,14 +282,14 @@ class Graph:
                            seed: int = 42, walk_id_base: int = 0, ragged: bool = False,
                            dispatch: str = "queue", rows=None, out=None,
                            direction: str = "forward"):
-        """Walks of uneven lengths and mixed hop biases in one persistent
-        launch. hop_biases: list of (kind, tau, p, q); max_lens: int32[W] or
+        """Walks of uneven lengths and mixed hop biases. hop_biases: list of (kind, tau, p, q); max_lens: int32[W] or
         None; bias_idx: uint8[W] or None (walk id mod len(hop_biases)).
         Returns (nodes, ts, len, row): rows of width max_len (row None), or,
         with ragged=True, packed rows starting at row[i] (int64[W + 1]; pass
         rows=(row, total) from row_offsets to skip computing them).
-        dispatch "queue" (persistent work queue) or "full_walk" (one thread
-        per walk, no queue); direction "forward" or "backward"."""
+        dispatch "queue" (or "auto": walk blocks of one bias each, with bias_idx
+        a persistent work queue) or "full_walk" (one thread per walk, no queue);
+        direction "forward" or "backward"."""
         W, L = int(num_walks), int(max_len)
         nb = len(hop_biases)  # the library rejects 0 or more than MAX_BIASES
         biases = (_Bias * MAX_BIASES)()

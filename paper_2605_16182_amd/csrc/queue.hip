@@ -257,12 +257,11 @@ struct Live {
 
 // Hops of the live walks after their start (k_coop_start and
 // k_compact_live leave them in `live`, n_live of them): the work queue
-// without the start pick, so a lane that takes a walk only loads its state
-// and the kernel keeps the registers of the full-walk kernel. ROWS: each
-// lane writes its walk's whole output row, four slots per store, padding
-// included; otherwise the rows were pre-filled. node2vec and mixed kinds
-// keep a walk's current four slots in an LDS ring (as k_walk_full) and are
-// held to 4 waves per SIMD: 4.47 ms against 5.00 with the slots in
+// without the start pick, so a lane that takes a walk only loads its state.
+// ROWS: each lane writes its walk's whole output row, four slots per store,
+// padding included; otherwise the rows were pre-filled. node2vec and mixed kinds
+// keep a walk's current four slots in an LDS ring and are held to 4 waves per
+// SIMD: 4.47 ms against 5.00 with the slots in
 // registers at 3 waves (2M walks of length 40, 100M-edge graph). The other
 // kinds keep the slots in registers at the occupancy their registers give:
 // there the ring and more waves measured slower (exponential 5.33 against

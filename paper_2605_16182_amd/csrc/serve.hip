@@ -430,8 +430,9 @@ void worker_loop(tw_server* S) {
             if (!S->inflight.empty()) {
                 // a launch is running: poll its event. A sleep ends about 50 us
                 // late (the kernel's timer slack), so a short one polls every 55
-                // us: with 50 us, every 105, a 500k-edge batch with 16 requests
-                // took 1.59 ms instead of 1.42
+                // us; with 50 us, every 105, a 500k-edge batch with 16 requests
+                // took 1.38 to 1.41 ms instead of 1.32 to 1.33 (runs of one form
+                // differ by 1 to 7 %)
                 lk.unlock();
                 std::this_thread::sleep_for(std::chrono::microseconds(5));
                 lk.lock();

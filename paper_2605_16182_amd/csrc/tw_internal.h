@@ -548,11 +548,11 @@ tw_status check_walk_params(const tw_walk_params* p, Error& err);
 // host table should be pinned and must stay untouched until the launch's
 // copy has run).
 size_t serve_table_bytes(int n);
-// Enqueue the padding and the walks of n requests (1..1024) in one launch;
-// *d_hops accumulates the launch's hops; request r's error words are
-// d_err[2 r] (a start node out of range) and d_err[2 r + 1] (node2vec
-// trial-cap hits), which the caller clears before the launch (d_err holds
-// at least 4 words). One large forward request runs the full-walk kernel.
+// Enqueue the walks of n requests (1..1024) in one launch, which pads their rows
+// or (wide rows) follows a fill of them; *d_hops accumulates the launch's hops;
+// request r's error words are d_err[2 r] (a start node out of range) and d_err[2 r
+// + 1] (node2vec trial-cap hits), which the caller clears before the launch (d_err
+// holds at least 4 words). One large forward request runs the full-walk kernel.
 // rev: backward requests (g is the in-view). Weight-based requests of one
 // launch share one time scale (tau).
 tw_status serve_launch(tw_graph* g, const ServeReq* reqs, int n, void* d_table, void* h_table,

@@ -32,8 +32,8 @@ __global__ void k_fill_outputs(int32_t* __restrict__ nodes, int64_t* __restrict_
 // Large launches are bound by the random lines they read and the lines they
 // write (4M exponential walks of length 80 on 100M edges: 5.6 TB/s of them, a
 // copy reaches 4.7), small ones by the chain of dependent loads; what helps is
-// wavefronts in flight (66 VGPRs for exponential hops, 75 for node2vec, 6.4 KB
-// of LDS: 5 to 6 a SIMD) and whole sectors in the writes. Against one walk per
+// wavefronts in flight (68 VGPRs for exponential hops, 76 to 78 for node2vec, 6.4
+// KB of LDS: 6 a SIMD) and whole sectors in the writes. Against one walk per
 // lane that padded its own row in chunks of four, with FP64 constants hoisted
 // into 128 VGPRs (4 a SIMD): that launch 3.75 -> 2.96 ms; 1M uniform walks of 25
 // slots on an undirected graph 817 -> 605 us (rows of any width are no longer
@@ -241,8 +241,9 @@ struct Candidates {
 // Gamma_t of the node of record r: forward the groups after t, backward (on
 // the in-view) those before t; false when there is none. rate: the pick reads
 // the first candidate's timestamp. (node2vec, which reads the group's record in
-// every trial, searches as ever: the shortcut took its kernel from 79 to 81
-// VGPRs, five wavefronts a SIMD instead of six.)
+// every trial, searches as ever: its kernels take 76 to 80 VGPRs, backward batches
+// with linear or exponential starts 82, and from 81 on five wavefronts a SIMD fit
+// instead of six.)
 template <bool REV>
 __device__ __forceinline__ bool candidates(const WalkArgs& a, const NodeRec& r, int64_t t,
                                            bool rate, bool n2v, Candidates& c) {
@@ -435,7 +436,7 @@ k_walk_full(const WalkArgs a) {
 // `only`-th walks of every stretch, with that bias's kernel (8M walks of
 // lengths 5-120 and six biases on a 40M-record graph: 12.7 ms with per-lane
 // biases on a work queue and a fill pass before it, 10.0 with one launch of
-// this kernel at 128 VGPRs, 7.4 with one launch a bias); else the blocks of a
+// this kernel at 128 VGPRs, 6.95 with one launch a bias); else the blocks of a
 // stretch go to one XCD (every eighth workgroup), where the lines that
 // their rows share meet in its L2. The blocks pad their rows unless the outputs
 // are pre_filled.

@@ -81,8 +81,9 @@ constexpr int WALK_THREADS = 256;
 
 // Kernels are instantiated per hop kind HK and start kind SK (-1: read at
 // run time). A fixed kind leaves only that picker's arithmetic in the
-// kernel: the full-walk kernel takes 58 VGPRs for uniform and linear hops and
-// 66 for exponential ones, against 92 for the kernel that carries every picker.
+// kernel: the full-walk kernel takes 62 VGPRs for uniform and linear hops and
+// 68 for exponential ones, against 97 for the serving kernel, which carries every
+// picker.
 template <int HK>
 __device__ __forceinline__ HopBias fixed_hop(HopBias h) {
     if (HK >= 0) h.kind = HK;
